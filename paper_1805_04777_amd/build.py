@@ -49,6 +49,9 @@ def _units():
                       [f"-DCRF_BWD_K={k}"]))
         units.append((os.path.join(CSRC, "blur.hip"), os.path.join(BUILD, f"blur_k{k}.o"),
                       [f"-DCRF_BLUR_K={k}"]))
+        if k >= 3:
+            units.append((os.path.join(CSRC, "group.hip"), os.path.join(BUILD, f"group_k{k}.o"),
+                          [f"-DCRF_GROUP_K={k}"]))
     for name in ("aux", "backward", "features", "api"):
         units.append((os.path.join(CSRC, f"{name}.hip"), os.path.join(BUILD, f"{name}.o"), []))
     return units

@@ -25,7 +25,6 @@ constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
-
 constexpr double kLog2eD = 1.4426950408889634073599;
 constexpr size_t kLdsLimit = 160 * 1024;  // gfx950 LDS per work-group
 // Most class groups the adjoint message splits its classes into (at least 4
@@ -289,11 +288,19 @@ hipError_t launch_ring(const IterArgs& a, int k, hipStream_t s) {
     switch (k) {
         case 3: return launch_ring_k3(a, s);
         case 5: return launch_ring_k5(a, s);
-        case 7: {
-            // Potts without a centre tap or features: the quad form
-            const hipError_t e = launch_quad_k7(a, s);
-            return e == hipErrorNotSupported ? launch_ring_k7(a, s) : e;
-        }
+        default: return hipErrorNotSupported;
+    }
+}
+
+hipError_t launch_group(const GroupArgs& a, int k, hipStream_t s) {
+    switch (k) {
+        case 3: return launch_group_k3(a, s);
+        case 5: return launch_group_k5(a, s);
+        case 7: return launch_group_k7(a, s);
+        case 9: return launch_group_k9(a, s);
+        case 11: return launch_group_k11(a, s);
+        case 13: return launch_group_k13(a, s);
+        case 15: return launch_group_k15(a, s);
         default: return hipErrorNotSupported;
     }
 }
@@ -326,13 +333,12 @@ TileConfig pick_tile(int k, int C, bool colour, bool compat) {
 // the parameters (compatibility, centre, taps); this sets its sizes and
 // tiles, and `as`, the copy with the tiling of the streamed kernel.
 // `bufs` are the Q buffers the launches read or write besides the unary.
-// streamed: whether the streamed kernel runs the iterations (k = 3..7,
+// streamed: whether the streamed kernel can run the first iteration (k = 3..7,
 // C = 19 or 21, whole float2 rows, unary rows in 16-byte pieces, buffers
 // under 2 GB, the LDS within bounds).
-void plan_unpooled(IterArgs& a, IterArgs& as, IterArgs& ar, bool& streamed, bool& ring,
-                   size_t& lds_s, TileConfig tile, bool mat, int k, int B, int C, int H, int W,
-                   const float* unary, const float* image, const float* kmat,
-                   std::initializer_list<const void*> bufs) {
+void plan_unpooled(IterArgs& a, IterArgs& as, bool& streamed, size_t& lds_s, TileConfig tile,
+                   bool mat, int k, int B, int C, int H, int W, const float* unary,
+                   const float* image, const float* kmat, std::initializer_list<const void*> bufs) {
     a.C = C;
     a.planes = C;
     a.H = H;
@@ -356,43 +362,85 @@ void plan_unpooled(IterArgs& a, IterArgs& as, IterArgs& ar, bool& streamed, bool
     as.tiles_x = (W + kStreamTW - 1) / kStreamTW;
     as.tiles_per_img = as.tiles_x * ((H + kStreamRows - 1) / kStreamRows);
     as.ntiles = as.tiles_per_img * B;
-    // the later streamed iterations on half-height tiles, two work-groups
-    // per CU (the first one stages all classes at once and keeps stream_kernel)
-    ar = as;
-    ar.tiles_per_img = as.tiles_x * ((H + kRingRows - 1) / kRingRows);
-    ar.ntiles = ar.tiles_per_img * B;
-    ring = streamed && ring_lds_bytes(k, C, C == 19 ? 4 : 3, a.mu != nullptr) <= kLdsLimit;
 }
 
-// Ring launches for the learnable-feature iterations (Sec. 4.2, "+T") over
-// B x C x H x W: true and `ar` set when the shapes allow them (k = 3..7,
-// C = 19 or 21, 1..kMaxFeat feature planes, whole float2 rows with W a
-// multiple of 4, the unary 16-byte aligned, buffers under 2 GB, the LDS
-// within bounds); every iteration then reads Q_t (no first-iteration form).
-bool plan_feature_ring(IterArgs& ar, const convcrf_params& p, const float* unary,
-                       const float* image, const float* mu_dev, int B, int C, int H, int W,
-                       std::initializer_list<const void*> bufs) {
-    const int k = p.filter_size, D = p.feature_dim;
-    if (k < 3 || k > 7 || D < 1 || D > kMaxFeat || (size_t)D * H * W * 4 >= (1ull << 31))
-        return false;
-    IterArgs a{}, as{};
+// Whether the lane-group rounds take B x C x H x W (any class count, width
+// and alignment; each image's planes under 2 GB, which buffer loads address).
+bool group_ok(int k, int C, int H, int W) {
+    return k >= 3 && (size_t)std::max(C, kMaxFeat) * H * W * 4 < (1ull << 31);
+}
+
+GroupArgs group_args(const convcrf_params& p, const float* unary, const float* image,
+                     const float* mu_dev, int B, int C, int H, int W) {
+    GroupArgs g{};
+    g.unary = unary;
+    g.image = image;
+    g.sfeat = p.features;
+    g.mu = mu_dev;
+    g.B = B;
+    g.C = C;
+    g.H = H;
+    g.W = W;
+    g.D = p.features ? p.feature_dim : 0;
+    g.include_center = p.include_center;
+    g.center_w = (float)((double)p.w_app + (double)p.w_smooth);
+    g.neg_beta = (float)(-kLog2eD / (2.0 * (double)p.theta_beta * p.theta_beta));
+    g.neg_gamma = (float)(-kLog2eD / (2.0 * (double)p.theta_gamma * p.theta_gamma));
+    g.w_smooth = p.w_smooth;
+    fill_taps(p, 1, g.taps);
+    return g;
+}
+
+// One round of the unpooled mean-field that reads Q_t: on lane groups, or for
+// narrow windows with 19 or 21 classes, W a multiple of 4 and aligned tensors
+// (`bufs`: the Q buffers the rounds read or write) on the ring kernel.
+struct Round {
+    bool ok = false;      // whether either takes these sizes
+    bool ring = false;
+    IterArgs ar{};
+    GroupArgs ga{};
+};
+
+Round plan_round(const convcrf_params& p, const float* unary, const float* image,
+                 const float* mu_dev, int B, int C, int H, int W,
+                 std::initializer_list<const void*> bufs) {
+    Round r;
+    const int k = p.filter_size;
+    r.ok = group_ok(k, C, H, W);
+    if (!r.ok) return r;
+    r.ga = group_args(p, unary, image, mu_dev, B, C, H, W);
+    bool aligned = reinterpret_cast<uintptr_t>(unary) % 16 == 0 && W % 4 == 0;
+    for (const void* b : bufs) aligned = aligned && reinterpret_cast<uintptr_t>(b) % 8 == 0;
+    r.ring = (k == 3 || k == 5) && (C == 19 || C == 21) && aligned &&
+             ring_lds_bytes(k, C, C == 19 ? 4 : 3, mu_dev != nullptr, r.ga.D) <= kLdsLimit;
+    if (!r.ring) return r;
+    IterArgs& a = r.ar;
+    a.unary = unary;
+    a.feat = image;
     a.mu = mu_dev;
+    a.C = a.planes = C;
+    a.H = H;
+    a.W = W;
+    a.tiles_x = (W + kStreamTW - 1) / kStreamTW;
+    a.tiles_per_img = a.tiles_x * ((H + kRingRows - 1) / kRingRows);
+    a.ntiles = a.tiles_per_img * B;
     a.include_center = p.include_center;
-    a.neg_beta = (float)(-kLog2eD / (2.0 * (double)p.theta_beta * p.theta_beta));
-    a.center_w = (float)((double)p.w_app + (double)p.w_smooth);
-    fill_taps(p, 1, a.taps);
-    bool streamed = false, ring = false;
-    size_t lds_s = 0;
-    plan_unpooled(a, as, ar, streamed, ring, lds_s, TileConfig{32, 2, 32}, false, k, B, C, H, W,
-                  unary, image, nullptr, bufs);
-    if (!ring || ring_lds_bytes(k, C, C == 19 ? 4 : 3, mu_dev != nullptr, D) > kLdsLimit)
-        return false;
-    ar.sfeat = p.features;
-    ar.D = D;
-    ar.neg_gamma = (float)(-kLog2eD / (2.0 * (double)p.theta_gamma * p.theta_gamma));
-    ar.w_smooth = p.w_smooth;
-    ar.first = 0;
-    return true;
+    a.sfeat = p.features;
+    a.D = r.ga.D;
+    a.neg_gamma = r.ga.neg_gamma;
+    a.w_smooth = p.w_smooth;
+    a.mode = kModeUpdate;
+    a.vec = 1;
+    a.neg_beta = r.ga.neg_beta;
+    a.center_w = r.ga.center_w;
+    a.taps = r.ga.taps;
+    return r;
+}
+
+hipError_t launch_round(Round& r, const float* src, float* dst, int k, hipStream_t stream) {
+    r.ar.src = r.ga.src = src;
+    r.ar.dst = r.ga.dst = dst;
+    return r.ring ? launch_ring(r.ar, k, stream) : launch_group(r.ga, k, stream);
 }
 
 // Arguments of the learnable-feature update over B x C x H x W.
@@ -425,7 +473,38 @@ FeatArgs feat_args(const convcrf_params& p, const float* unary, const float* ima
     return f;
 }
 
-// Upload mu (C*C floats) if it differs from what the device holds.
+// The compatibility as the kernels take it: a column less its (lower) median
+// where that at least halves the column's magnitude, as near Potts, where
+// little more than the diagonal is left.  Adding a constant to a column of mu
+// adds the same amount to every class's logit, which the softmax removes, and
+// to dL/dM a multiple of sum_l dL/dZ(l) = 0; left in, it rounds the logits at
+// the scale of the whole message.  The median, not the mean, so that one large
+// entry leaves the others as they are; a column with a NaN or an infinite
+// median stays.
+void centre_compat(const float* mu, int C, float* out) {
+    for (int m = 0; m < C; ++m) {
+        float col[kMaxC];
+        bool ok = true;
+        for (int l = 0; l < C; ++l) {
+            col[l] = mu[l * C + m];
+            ok = ok && !std::isnan(col[l]);
+        }
+        float c = 0.f;
+        if (ok) {
+            std::sort(col, col + C);
+            c = col[(C - 1) / 2];
+            double before = 0.0, after = 0.0;
+            for (int l = 0; l < C; ++l) {
+                before += std::fabs((double)col[l]);
+                after += std::fabs((double)col[l] - c);
+            }
+            if (!(2.0 * after <= before) || !std::isfinite(before)) c = 0.f;
+        }
+        for (int l = 0; l < C; ++l) out[l * C + m] = mu[l * C + m] - c;
+    }
+}
+
+// Upload mu (C*C floats, centred) if it differs from what the device holds.
 convcrf_status upload_mu(convcrf_ctx* ctx, const float* mu, int C, hipStream_t stream) {
     const size_t n = (size_t)C * C;
     if (ctx->mu_last.size() == n && std::memcmp(ctx->mu_last.data(), mu, n * sizeof(float)) == 0)
@@ -450,7 +529,7 @@ convcrf_status upload_mu(convcrf_ctx* ctx, const float* mu, int C, hipStream_t s
         e = hipEventSynchronize(ctx->mu_copied);  // previous upload has left the staging
         if (e != hipSuccess) return hip_fail(ctx, e, "hipEventSynchronize");
     }
-    std::memcpy(ctx->mu_pinned, mu, n * sizeof(float));
+    centre_compat(mu, C, ctx->mu_pinned);
     e = hipMemcpyAsync(ctx->mu.p, ctx->mu_pinned, n * sizeof(float), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipMemcpyAsync(compat)");
     e = hipEventRecord(ctx->mu_copied, stream);
@@ -601,7 +680,7 @@ convcrf_status upload_mu_noalloc(convcrf_ctx* ctx, Workspace& w, const float* mu
     convcrf_status st = take(ctx, w, unused, sizeof(float) * (size_t)C * C, &dst);
     if (st != CONVCRF_OK) return st;
     CompatBlock blk{};
-    std::memcpy(blk.v, mu, sizeof(float) * (size_t)C * C);
+    centre_compat(mu, C, blk.v);
     const hipError_t e = launch_copy_compat(blk, C * C, static_cast<float*>(dst), stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "copying the compatibility matrix");
     *out = static_cast<const float*>(dst);
@@ -841,18 +920,22 @@ convcrf_status meanfield_impl(convcrf_ctx* ctx, const float* unary, const float*
         // the staged Q planes live in q_out and the workspace
         f.vec4 = f.vec4 && reinterpret_cast<uintptr_t>(q_out) % 16 == 0 &&
                  reinterpret_cast<uintptr_t>(ws) % 16 == 0;
-        IterArgs ar{};
-        const bool ring = plan_feature_ring(ar, p, unary, image, mu_dev, B, C, H, W, {q_out, ws});
+        // (at 19 and 21 classes an output off an 8-byte boundary selects the
+        // general kernel: the one input on which both can be compared)
+        Round round;
+        if ((C != 19 && C != 21) || reinterpret_cast<uintptr_t>(q_out) % 8 == 0)
+            round = plan_round(p, unary, image, mu_dev, B, C, H, W, {q_out, ws});
         float* q0 = iters % 2 == 0 ? q_out : ws;
         st = launch(ctx, kSoftmax, stream, "softmax",
                     [&] { return launch_softmax(unary, q0, B, C, H * W, stream); });
         if (st != CONVCRF_OK) return st;
         const float* cur = q0;
         for (int t = 0; t < iters; ++t) {
-            f.src = ar.src = cur;
-            f.dst = ar.dst = ((iters - 1 - t) % 2 == 0) ? q_out : ws;
+            f.src = cur;
+            f.dst = ((iters - 1 - t) % 2 == 0) ? q_out : ws;
             st = launch(ctx, kFeatIter, stream, "feature_iter", [&] {
-                return ring ? launch_ring(ar, k, stream) : launch_feat_update(f, k, stream);
+                return round.ok ? launch_round(round, f.src, f.dst, k, stream)
+                                : launch_feat_update(f, k, stream);
             });
             if (st != CONVCRF_OK) return st;
             cur = f.dst;
@@ -887,10 +970,10 @@ convcrf_status meanfield_impl(convcrf_ctx* ctx, const float* unary, const float*
                 if (st != CONVCRF_OK) return st;
             }
         }
-        IterArgs as, ar;                      // the streamed and ring launches' tilings
-        bool streamed = false, ring = false;
+        IterArgs as;                          // the streamed launch's tiling
+        bool streamed = false;
         size_t lds_s = 0;
-        plan_unpooled(a, as, ar, streamed, ring, lds_s, tile, mat, k, B, C, H, W, unary, image,
+        plan_unpooled(a, as, streamed, lds_s, tile, mat, k, B, C, H, W, unary, image,
                       static_cast<const float*>(ctx->kmat.p), {q_out, wsp});
         // Resident variant: all iterations in one launch when every tile's
         // work-group fits on the device at once (Potts): the tile stays in
@@ -954,15 +1037,33 @@ convcrf_status meanfield_impl(convcrf_ctx* ctx, const float* unary, const float*
         // the last iteration writes q_out; earlier ones alternate so that
         // source and destination always differ
         const float* cur = unary;
+        // The rounds read Q_t.  The first one's is softmax(U), which the
+        // streamed kernel takes on the fly: worth it while its tiles (one
+        // work-group per CU) all run at once, as the pass over U that it
+        // saves then costs more than its lower rate (512 x 512, 21 classes:
+        // 24.5 against 9.0 + 18.9 us); on more tiles the separate pass wins
+        // (8 frames: 217 against 55 + 138 us).
+        Round round;
+        if (!mat && iters > 1)
+            round = plan_round(p, unary, image, mu_dev, B, C, H, W, {q_out, wsp});
+        const bool first = streamed && (!round.ok || as.ntiles <= ctx->num_cus);
+        if (round.ok && !first) {
+            float* q0 = iters % 2 == 0 ? q_out : ws;
+            st = launch(ctx, kSoftmax, stream, "softmax",
+                        [&] { return launch_softmax(unary, q0, B, C, H * W, stream); });
+            if (st != CONVCRF_OK) return st;
+            cur = q0;
+        }
         for (int t = 0; t < iters; ++t) {
             float* dst = ((iters - 1 - t) % 2 == 0) ? q_out : ws;
-            a.src = as.src = ar.src = cur;
-            a.dst = as.dst = ar.dst = dst;
-            a.first = as.first = ar.first = t == 0;
-            st = launch(ctx, mat ? kMatIter : (t == 0 ? kFusedFirst : kFused), stream,
+            a.src = as.src = cur;
+            a.dst = as.dst = dst;
+            a.first = as.first = t == 0;
+            const bool one = t == 0 && (first || !round.ok);
+            st = launch(ctx, mat ? kMatIter : one ? kFusedFirst : kFused, stream,
                         mat ? "materialised_iter" : "fused_iter", [&] {
-                            if (ring && t > 0) return launch_ring(ar, k, stream);
-                            return streamed ? launch_stream(as, k, lds_s, stream)
+                            if (t == 0 && first) return launch_stream(as, k, lds_s, stream);
+                            return round.ok ? launch_round(round, cur, dst, k, stream)
                                             : launch_iter(a, k, mat, tile, lds, stream);
                         });
             if (st != CONVCRF_OK) return st;
@@ -1393,16 +1494,21 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
                 if (st != CONVCRF_OK) return st;
             }
         }
+    } else if (run && group_ok(k, C, H, W)) {
+        // every round from Q^0 = softmax(U) on
+        Round round = plan_round(p, unary, image, mu_dev, B, C, H, W, {qbase});
+        for (int t = 0; t < iters; ++t) {
+            st = launch(ctx, D > 0 ? kFeatIter : kFused, stream, D > 0 ? "feature_iter" : "fused_iter",
+                        [&] { return launch_round(round, qs(t), qs(t + 1), k, stream); });
+            if (st != CONVCRF_OK) return st;
+        }
     } else if (run && p.features) {
         FeatArgs f = feat_args(p, unary, image, mu_dev, B, C, H, W);
-        IterArgs ar{};
-        const bool ring = plan_feature_ring(ar, p, unary, image, mu_dev, B, C, H, W, {qbase});
         for (int t = 0; t < iters; ++t) {
-            f.src = ar.src = qs(t);
-            f.dst = ar.dst = qs(t + 1);
-            st = launch(ctx, kFeatIter, stream, "feature_iter", [&] {
-                return ring ? launch_ring(ar, k, stream) : launch_feat_update(f, k, stream);
-            });
+            f.src = qs(t);
+            f.dst = qs(t + 1);
+            st = launch(ctx, kFeatIter, stream, "feature_iter",
+                        [&] { return launch_feat_update(f, k, stream); });
             if (st != CONVCRF_OK) return st;
         }
     } else if (run) {
@@ -1415,20 +1521,17 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
         const TileConfig tile = pick_tile(k, C, true, mu_dev != nullptr);
         if (tile.rows == 0) return fail(ctx, CONVCRF_E_UNSUPPORTED, "window and classes exceed LDS");
         const size_t lds = iter_lds_bytes(k, C, tile, true, mu_dev != nullptr);
-        IterArgs as, ar;
-        bool streamed = false, ring = false;
+        IterArgs as;
+        bool streamed = false;
         size_t lds_s = 0;
-        plan_unpooled(a, as, ar, streamed, ring, lds_s, tile, false, k, B, C, H, W, unary, image,
-                      nullptr, {qbase});
+        plan_unpooled(a, as, streamed, lds_s, tile, false, k, B, C, H, W, unary, image, nullptr,
+                      {qbase});
         for (int t = 0; t < iters; ++t) {
-            a.src = as.src = ar.src = t == 0 ? unary : qs(t);
-            a.dst = as.dst = ar.dst = qs(t + 1);
-            a.first = as.first = ar.first = t == 0;
-            st = launch(ctx, t == 0 ? kFusedFirst : kFused, stream, "fused_iter", [&] {
-                if (ring && t > 0) return launch_ring(ar, k, stream);
-                return streamed ? launch_stream(as, k, lds_s, stream)
-                                : launch_iter(a, k, false, tile, lds, stream);
-            });
+            a.src = t == 0 ? unary : qs(t);
+            a.dst = qs(t + 1);
+            a.first = t == 0;
+            st = launch(ctx, t == 0 ? kFusedFirst : kFused, stream, "fused_iter",
+                        [&] { return launch_iter(a, k, false, tile, lds, stream); });
             if (st != CONVCRF_OK) return st;
         }
     }

@@ -12,6 +12,7 @@ namespace convcrf {
 // Largest window side k and class count the kernels are built for.
 constexpr int kMaxK = 15;
 constexpr int kMaxC = 24;
+constexpr int kMaxFeat = 4;   // learnable feature planes
 
 // Output tile: `width` (32, or 16 for small grids) columns by `rows` rows;
 // each thread owns `pix` (2 or 4) horizontally adjacent pixels of one row.
@@ -63,8 +64,8 @@ struct IterArgs {
     unsigned int* sync;   // [0] error flag, [1 + tile] rings published by each
                           // tile; all zero before the launch
     int include_center;   // add (w_app + w_smooth) Q_p to the message
-    // learnable smoothness features (ring update only): F [B][D][H][W] or
-    // null; the smoothness Gaussian is then w_smooth exp2(neg_gamma |F_p -
+    // learnable smoothness features (ring update, and pooled pmsg_kernel):
+    // F [B][D][H][W] or null; the smoothness Gaussian is then w_smooth exp2(neg_gamma |F_p -
     // F_q|^2) instead of taps.smooth
     const float* sfeat;
     int D;
@@ -100,7 +101,7 @@ inline size_t stream_lds_bytes(int k, int C, bool with_compat) {
                             (with_compat ? ((size_t)C * C + 63) / 64 * 64 : 0) + 256);
 }
 
-// Ring update (the later iterations, k <= 7, C = 19 or 21): tiles of
+// Ring update (the later iterations, k = 3 or 5, C = 19 or 21): tiles of
 // kStreamTW x kRingRows pixels, 256 threads, the class chunks cycled through
 // three LDS slots and the unary loaded into registers, so that two
 // work-groups share a CU; LDS bytes of a work-group (three slots of CH
@@ -110,19 +111,17 @@ constexpr int kRingRows = 8, kRingSlots = 3;
 constexpr int ring_plane(int k) {
     return ((kRingRows + k - 1) * iter_lds_stride(k, 2, kStreamTW) + 63) / 64 * 64;
 }
-// The quad form of the k = 7 ring update (lane pairs on 4-pixel quads)
-// reads its staged rows with 16-byte LDS reads, so its row stride is padded
-// to a multiple of 4 floats; its plane is the same size as ring_plane(7).
-constexpr int kQuadStride = 72;
-constexpr int quad_plane() { return ((kRingRows + 6) * kQuadStride + 63) / 64 * 64; }
-static_assert(quad_plane() == ring_plane(7), "the quad update shares the ring's LDS plan");
-// and the first round's, on the streamed tiles, the same size as stream_plane(7)
-constexpr int quad_first_plane() { return ((kStreamRows + 6) * kQuadStride + 63) / 64 * 64; }
-static_assert(quad_first_plane() == stream_plane(7), "the quad first round shares the streamed LDS plan");
 inline size_t ring_lds_bytes(int k, int C, int CH, bool with_compat, int D = 0) {
     return sizeof(float) * ((size_t)(kRingSlots * CH + 3 + D) * ring_plane(k) +
                             (with_compat ? ((size_t)C * C + 63) / 64 * 64 : 0) + 256);
 }
+
+// The quad form of the first update (k = 7, lane pairs on 4-pixel quads)
+// reads its staged rows with 16-byte LDS reads, so its row stride is padded
+// to a multiple of 4 floats; its plane is the same size as stream_plane(7).
+constexpr int kQuadStride = 72;
+constexpr int quad_first_plane() { return ((kStreamRows + 6) * kQuadStride + 63) / 64 * 64; }
+static_assert(quad_first_plane() == stream_plane(7), "the quad first round shares the streamed LDS plan");
 
 // Pooled message of the blur path: tiles of 16 x 8 cells, one wavefront per
 // window row (64 k threads), chunks of at most kPmsgClasses classes; LDS
@@ -158,9 +157,8 @@ inline size_t iter_lds_bytes(int k, int C, TileConfig t, bool with_colour, bool 
 // (hipSuccess) or not (hipErrorNotSupported / hipErrorCooperativeLaunchTooLarge).
 // launch_rstream runs all a.iters iterations in one cooperative launch on
 // the tiles of launch_stream (the resident variant; probe as above).
-// launch_stream runs one update with the staging streamed under the
-// computation (k = 3, 5, 7, C = 19 or 21, vector path; the first iteration
-// applies softmax(U) in LDS); hipErrorNotSupported when the arguments are
+// launch_stream runs the first update, softmax(U) applied in LDS (k = 3, 5,
+// 7, C = 19 or 21, vector path); hipErrorNotSupported when the arguments are
 // outside that.
 #define CONVCRF_DECLARE_ITER(K)                                              \
     hipError_t launch_iter_k##K(const IterArgs& a, bool materialised,        \
@@ -186,11 +184,69 @@ CONVCRF_DECLARE_ITER(11)
 CONVCRF_DECLARE_ITER(13)
 CONVCRF_DECLARE_ITER(15)
 #undef CONVCRF_DECLARE_ITER
-// The k = 7 ring update in its quad form (Potts, no centre tap, no features;
-// C = 19 or 21); hipErrorNotSupported outside that.
-hipError_t launch_quad_k7(const IterArgs& a, hipStream_t stream);
-// The first round (softmax(U) staged in LDS) in the same quad layout.
+// The first update at k = 7 in its quad form (Potts, no centre tap, no
+// features; C = 19 or 21); hipErrorNotSupported outside that.
 hipError_t launch_quad_first_k7(const IterArgs& a, hipStream_t stream);
+
+// ---- one round on lane groups (group.hip): a group of G lanes shares four
+// pixels and splits the k x k window; NF full window rows and NT taps of the
+// centre row per lane, tiles of TW x TH pixels on NWAVE wavefronts, staged
+// rows LS floats apart in planes of PLANE floats (whole 64-float loads), LDS
+// reads DEPTH - 1 steps ahead.
+constexpr int kGroupCH = 3, kGroupSlots = 3;   // classes a chunk, chunk slots in LDS
+template <int K>
+struct GroupShape {
+    static constexpr int G = K <= 7 ? 2 : K <= 13 ? 4 : 8;
+    static constexpr bool PART = G > 1 && (K - 1) % G == 0;
+    static constexpr int NF = PART ? (K - 1) / G : (K + G - 1) / G;
+    static constexpr int NT = PART ? (K - 1) / G : 0;
+    static constexpr int NWAVE = G <= 4 ? 4 : 8;
+    static constexpr int TW = G <= 4 ? 64 : 32;
+    static constexpr int TH = NWAVE * (64 / G) / (TW / 4);
+    // staged columns start XO left of the tile, a whole 16-byte piece
+    static constexpr int XO = ((K - 1) / 2 + 3) / 4 * 4;
+    // rows 80 floats apart (48 for the narrow tile): four rows are a multiple
+    // of 64 floats, the distance at which LDS serves two rows at full rate
+    static constexpr int LS = TW == 64 ? 80 : 48;
+    static_assert(LS >= XO + TW + (K - 1) / 2 && 4 * LS % 64 == 0, "staged rows");
+    static constexpr int PLANE = ((TH + K - 1) * LS + 255) / 256 * 256;
+    // floats of a chunk: its planes, padded to the same count of loads for
+    // every wavefront (16 bytes a lane, or 4)
+    static constexpr int slot(bool a16) {
+        const int f = NWAVE * (a16 ? 256 : 64);
+        return (kGroupCH * PLANE + f - 1) / f * f;
+    }
+    static constexpr int DEPTH = K == 13 ? 2 : 3;
+    static constexpr bool LATE_U = K == 13;   // load the unary after the message
+};
+constexpr int kGroupTab = 256;                 // floats kept for the tap table
+static_assert(sizeof(TapTable) <= kGroupTab * sizeof(float), "the table fits");
+template <int K>
+constexpr size_t group_lds_bytes(int CM, int FD, bool a16, bool with_compat) {
+    return sizeof(float) * ((size_t)(kGroupSlots + 1) * GroupShape<K>::slot(a16) +
+                            (size_t)FD * GroupShape<K>::PLANE + kGroupTab +
+                            (with_compat ? (CM * ((CM + 3) / 4 * 4) + 63) / 64 * 64 : 0));
+}
+struct GroupArgs {
+    const float* src;     // Q_t [B][C][H][W]
+    const float* unary;   // U [B][C][H][W]
+    const float* image;   // [B][3][H][W]
+    const float* sfeat;   // learnable features [B][D][H][W], or null
+    const float* mu;      // device C x C compatibility, null = Potts
+    float* dst;           // Q_{t+1}
+    int B, C, H, W, D;
+    int include_center;
+    float center_w, neg_beta, neg_gamma, w_smooth;
+    TapTable taps;
+    int tiles_x, tiles_per_img, ntiles;   // set by the launcher
+};
+hipError_t launch_group_k3(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k5(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k7(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k9(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k11(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k13(GroupArgs a, hipStream_t stream);
+hipError_t launch_group_k15(GroupArgs a, hipStream_t stream);
 
 // Fill n words with zero (the flags of a resident launch: a kernel, not a
 // memset, so that the sequence may be captured in a graph).
@@ -307,7 +363,6 @@ hipError_t launch_blur_init(const BlurInitArgs& a, hipStream_t stream);
 // ---- learnable smoothness features (the "+T" variant): one update with
 // the smoothness Gaussian on |F_p - F_q|^2 of a feature map F [B][D][H][W]
 // instead of |p - q|^2.  32 x 8 tiles, one pixel per thread.
-constexpr int kMaxFeat = 4;
 struct FeatArgs {
     const float* src;    // Q_t [B][C][H][W]
     const float* unary;  // U [B][C][H][W]

@@ -19,9 +19,10 @@
 // The materialised variant reads the weights from a precomputed kernel
 // matrix instead of step 1 (the two-stage structure of Sec. 4.1).
 //
-// Also here: stream_kernel, the same update with the staging streamed under
-// the computation; rstream_kernel, its resident form (all iterations in one
-// launch); and pmsg_kernel, the message of the blur path on the pooled grid
+// Also here: stream_kernel and quad_first_kernel, the first update with
+// softmax(U) taken in LDS; ring_kernel, the later ones of narrow windows (all
+// others run on lane groups, group.hip);
+// rstream_kernel, all iterations in one launch; and pmsg_kernel, the message of the blur path on the pooled grid
 // (Sec. 4.2).
 
 #include "crf_internal.h"
@@ -287,8 +288,10 @@ void iter_kernel(const IterArgs a) {
     // With Potts the update is softmax(U + M) (the compatibility transform
     // -(sum M - M) differs from +M by a per-pixel constant), so the message
     // accumulates straight onto the unary, which is loaded here and arrives
-    // while the tile is being staged.
-    const bool unary_first = !general_compat;
+    // while the tile is being staged.  (A resident launch adds it at the end:
+    // it sums in the order of the lane groups that run the same rounds one
+    // launch each, so that the two agree bit for bit.)
+    const bool unary_first = !RES && !general_compat;
     const float* const unary_px = a.unary + cbase * HW + (size_t)y * W + xb;
     float acc[P][CM];
 #pragma unroll
@@ -311,7 +314,7 @@ void iter_kernel(const IterArgs a) {
 
     // ---- message: acc[i][c] = sum_d K(p_i, p_i + d) Q_t(p_i + d, c)
     for (int it = 0;; ++it) {
-    if (it > 0) {  // resident launch: the next iteration starts from U again
+    if (it > 0) {  // resident launch: the next iteration starts again
 #pragma unroll
         for (int i = 0; i < P; ++i)
 #pragma unroll
@@ -333,8 +336,9 @@ void iter_kernel(const IterArgs a) {
 
     // one window row of the message; unrolled over rows on the fused exact-C
     // path, rolled where the fully unrolled body would exceed the registers
-    constexpr bool kUnrollRows = !MAT && (EXACT || CM <= 16) && K <= 9;
-    auto window_row = [&](const int dy) {
+    constexpr bool kUnrollRows = !MAT && !(RES && K > 1) && (EXACT || CM <= 16) && K <= 9;
+    // taps dx in [lo, hi) of the row
+    auto window_row = [&](const int dy, const int lo = 0, const int hi = K) {
         const int row = ty + dy;
         float w[P][K];
         if constexpr (!MAT) {
@@ -388,7 +392,7 @@ void iter_kernel(const IterArgs a) {
 #pragma unroll
                 for (int dx = 0; dx < K; ++dx)
                     // the centre weight is 0; unrolled rows skip its FMA outright
-                    if (!kUnrollRows || dy * K + dx != CTR)
+                    if (dx >= lo && dx < hi && (!kUnrollRows || dy * K + dx != CTR))
                         acc[i][c] = fmaf(w[i][dx], q[i + dx], acc[i][c]);
         };
         const float* qrow = Qs + row * LS + col0;
@@ -409,7 +413,27 @@ void iter_kernel(const IterArgs a) {
             }
         }
     };
-    if constexpr (kUnrollRows) {
+    if constexpr (RES && K > 1) {
+        // the two halves of the window apart, each the full rows first
+        float half[P][CM];
+#pragma unroll 1
+        for (int dy = 0; dy < R; ++dy) window_row(dy);
+        window_row(R, 0, R);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < CM; ++c) {
+                half[i][c] = acc[i][c];
+                acc[i][c] = 0.f;
+            }
+#pragma unroll 1
+        for (int dy = R + 1; dy < K; ++dy) window_row(dy);
+        window_row(R, R + 1, K);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < CM; ++c) acc[i][c] = half[i][c] + acc[i][c];
+    } else if constexpr (kUnrollRows) {
 #pragma unroll
         for (int dy = 0; dy < K; ++dy) window_row(dy);
     } else {
@@ -483,6 +507,18 @@ void iter_kernel(const IterArgs a) {
             for (int j = 0; j < P; ++j)
 #pragma unroll
                 for (int c = 0; c < CM; ++c) fin[j][c] = z[j][c];
+        }
+        if constexpr (RES) {
+            float u[P][CM];
+#pragma unroll
+            for (int j = 0; j < P; ++j)
+#pragma unroll
+                for (int c = 0; c < CM; ++c) u[j][c] = 0.f;
+            if (pix_ok) load_pixels(u, unary_px, xb, fullv);
+#pragma unroll
+            for (int j = 0; j < P; ++j)
+#pragma unroll
+                for (int c = 0; c < CM; ++c) fin[j][c] += u[j][c];
         }
 #pragma unroll
         for (int j = 0; j < P; ++j) softmax_regs<CM, EXACT>(fin[j], C);
@@ -617,23 +653,18 @@ __device__ __forceinline__ void static_for(F&& f, std::integer_sequence<int, I..
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-// Fused update with the staging streamed under the computation (iterations
-// after the first; two pixels per thread on 64 x 16 tiles, all classes,
-// k <= 7).  Instead
-// of loading the whole halo'd tile before the message, every wave issues
-// buffer loads that write straight into LDS (no registers held): the three
-// colour planes and the first two chunks of class planes of Q_t.  As soon
-// as the colours have landed the work-group computes all of its pixels'
-// window weights (Eq. 4) into registers; then it applies them to the classes
-// chunk by chunk, each chunk starting when its planes have landed and
-// issuing the loads of the chunk two ahead, so that at most two chunks are
-// in flight and the early ones do not queue behind the late ones.  The
-// unary tile is loaded the same way, into the planes of chunks already
-// applied, and added in the epilogue (compatibility, softmax, store).
+// The first iteration on 64 x 16 tiles (two pixels per thread, all classes,
+// k <= 7), whose source is U itself.  Every wave issues buffer loads that
+// write straight into LDS (no registers held): the three colour planes and
+// then all class planes.  As soon as the colours have landed the work-group
+// computes all of its pixels' window weights (Eq. 4) into registers; once
+// everything has, each thread keeps the unary of its own pixels in registers,
+// the staged halo tile is turned into softmax(U) in place (Alg. 1
+// initialisation), and the message runs over the classes.
 //
 // Each staged plane is padded to whole 64-float DMA rows and every wave
 // issues the same number of loads per plane (a load past the plane goes to
-// a dummy LDS row), so that a wave waits for a chunk with one constant
+// a dummy LDS row), so that a wave waits for the colours with one constant
 // vmcnt.  Pixels outside the image get an out-of-range buffer offset, which
 // reads as zero: neighbours outside the image contribute nothing.
 // Loads per wave of chunk k (classes [k CH, min((k + 1) CH, C))), 0 past
@@ -694,11 +725,7 @@ __device__ __forceinline__ void message_chunk(const float* Qs, int ty, int col0,
     }
 }
 
-// FIRST: the first iteration, whose source is U itself: all planes are
-// loaded at once, each thread keeps the unary of its own pixels in
-// registers, and the staged halo tile is turned into softmax(U) in place
-// (Alg. 1 initialisation) before the message.
-template <int K, int CM, int CH, bool FIRST>
+template <int K, int CM, int CH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void stream_kernel(const IterArgs a) {
     using SS = StreamShape<K>;
@@ -712,11 +739,6 @@ void stream_kernel(const IterArgs a) {
     constexpr unsigned kOob = 0x80000000u;   // offset past any buffer: reads 0
 
     constexpr int MUP = (CM * CM + 63) / 64 * 64;   // compatibility, whole rows
-    // the unary tile [CM][ROWS x TW] goes to the planes of chunks 0 .. UCH - 1
-    // once they have been applied (the first chunk whose start frees enough)
-    constexpr int UCH = (CM * 1024 + CH * PLANE - 1) / (CH * PLANE);
-    static_assert(UCH < NCH, "the unary tile fits in the planes of the chunks before the last");
-    constexpr int NU = (CM * 4 + 7) / 8;         // 16-byte loads of 8 rows, per wave
     extern __shared__ float4 smem4[];
     float* const smem = reinterpret_cast<float*>(smem4);
     float* const Qs = smem;                      // [CM][PLANE]
@@ -769,20 +791,11 @@ void stream_kernel(const IterArgs a) {
         for (int s = 0; s < NJ; ++s)
             lds_dma(rf, voff[s], (int)(ch * HW * 4),
                     lds_addr(dst[s] >= 0 ? Cs + ch * PLANE + dst[s] : dummy));
-    auto issue_chunk = [&](int k) {
-        const int c_hi = (k + 1) * CH < CM ? (k + 1) * CH : CM;
-        for (int c = k * CH; c < c_hi; ++c)
+    for (int c = 0; c < CM; ++c)
 #pragma unroll
-            for (int s = 0; s < NJ; ++s)
-                lds_dma(rq, voff[s], (int)(c * HW * 4),
-                        lds_addr(dst[s] >= 0 ? Qs + c * PLANE + dst[s] : dummy));
-    };
-    if constexpr (FIRST) {
-        for (int k = 0; k < NCH; ++k) issue_chunk(k);
-    } else {
-        issue_chunk(0);
-        if (NCH > 1) issue_chunk(1);
-    }
+        for (int s = 0; s < NJ; ++s)
+            lds_dma(rq, voff[s], (int)(c * HW * 4),
+                    lds_addr(dst[s] >= 0 ? Qs + c * PLANE + dst[s] : dummy));
 
     const int tx = tid % TPR, ty = tid / TPR;
     const int col0 = tx * P;
@@ -792,9 +805,7 @@ void stream_kernel(const IterArgs a) {
     // ---- colours landed: the window weights of both pixels, all rows
     // (a wait beyond the 63 loads a wave can have outstanding is clamped:
     // the loads before the last 63 issued have completed by then)
-    __builtin_amdgcn_s_waitcnt(vm_wait(FIRST ? NJ * CM
-                                             : stream_chunk_loads(0, CM, CH, NJ) +
-                                                   stream_chunk_loads(1, CM, CH, NJ)));
+    __builtin_amdgcn_s_waitcnt(vm_wait(NJ * CM));
     __syncthreads();
     float w[K][P][K];
     {
@@ -826,65 +837,38 @@ void stream_kernel(const IterArgs a) {
     }
 
     float u[P][CM];
-    if constexpr (FIRST) {
-        // every plane landed: keep this thread's unary, then softmax(U) over
-        // the staged in-image positions (outside the image stays zero)
-        __builtin_amdgcn_s_waitcnt(vm_wait(0));
-        __syncthreads();
+    // every plane landed: keep this thread's unary, then softmax(U) over
+    // the staged in-image positions (outside the image stays zero)
+    __builtin_amdgcn_s_waitcnt(vm_wait(0));
+    __syncthreads();
 #pragma unroll
-        for (int c = 0; c < CM; ++c)
+    for (int c = 0; c < CM; ++c)
 #pragma unroll
-            for (int i = 0; i < P; ++i) u[i][c] = Qs[c * PLANE + (ty + R) * LS + col0 + R + i];
-        __syncthreads();
-        for (int pos = tid; pos < LH * LS; pos += 512) {
-            const int r = pos / LS, col = pos - (pos / LS) * LS;
-            const int gy = y0 - R + r, gx = x0 - R + col;
-            if (col >= LW || gy < 0 || gy >= H || gx < 0 || gx >= W) continue;
-            float z[CM];
+        for (int i = 0; i < P; ++i) u[i][c] = Qs[c * PLANE + (ty + R) * LS + col0 + R + i];
+    __syncthreads();
+    for (int pos = tid; pos < LH * LS; pos += 512) {
+        const int r = pos / LS, col = pos - (pos / LS) * LS;
+        const int gy = y0 - R + r, gx = x0 - R + col;
+        if (col >= LW || gy < 0 || gy >= H || gx < 0 || gx >= W) continue;
+        float z[CM];
 #pragma unroll
-            for (int c = 0; c < CM; ++c) z[c] = Qs[c * PLANE + pos];
-            softmax_regs<CM, true>(z, CM);
+        for (int c = 0; c < CM; ++c) z[c] = Qs[c * PLANE + pos];
+        softmax_regs<CM, true>(z, CM);
 #pragma unroll
-            for (int c = 0; c < CM; ++c) Qs[c * PLANE + pos] = z[c];
-        }
-        __syncthreads();
+        for (int c = 0; c < CM; ++c) Qs[c * PLANE + pos] = z[c];
     }
+    __syncthreads();
 
-    // ---- the message, chunk by chunk as the planes land
+    // ---- the message, chunk by chunk
     float acc[P][CM];
 #pragma unroll
     for (int i = 0; i < P; ++i)
 #pragma unroll
         for (int c = 0; c < CM; ++c) acc[i][c] = 0.f;
-    float* const Us = Qs;                        // [CM][ROWS x TW], from chunk UCH on
-    const rsrc_t ru = buffer_rsrc(a.unary + (size_t)b * CM * HW, (unsigned)(CM * HW * 4));
     static_for([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         constexpr int c_lo = k * CH;
         constexpr int c_hi = (k + 1) * CH < CM ? (k + 1) * CH : CM;
-        // chunk k landed.  Issued after its loads (at chunk k - 2) and
-        // before this wait: chunk k + 1 (at chunk k - 1), and the unary if
-        // it went out at chunk k - 2 or k - 1.
-        if constexpr (!FIRST) {
-            __builtin_amdgcn_s_waitcnt(vm_wait(stream_chunk_loads(k + 1, CM, CH, NJ) +
-                                               (UCH < k && k <= UCH + 2 ? NU : 0)));
-            __syncthreads();
-        }
-        if constexpr (!FIRST && k + 2 < NCH) issue_chunk(k + 2);
-        if constexpr (!FIRST && k == UCH) {
-            // every wave is past the chunks before k: their planes take the
-            // unary tile, plane c at Us + 1024 c, 256 / TW rows per load
-#pragma unroll
-            for (int s = 0; s < NU; ++s) {
-                const int j = wave + 8 * s;          // (plane, band of 256 / TW rows)
-                constexpr int LPR = TW / 4;          // lanes per row
-                const int c = j / 4, r = (j % 4) * (256 / TW) + lane / LPR, col = (lane % LPR) * 4;
-                const bool in = j < CM * 4 && y0 + r < H && x0 + col < W;
-                lds_dma16(ru, in ? (unsigned)(((y0 + r) * W + x0 + col) * 4) : kOob,
-                          (int)((j < CM * 4 ? c : 0) * HW * 4),
-                          lds_addr(j < CM * 4 ? Us + j * 256 : dummy));
-            }
-        }
         message_chunk<K, P, LS, PLANE, CM, c_lo, c_hi>(Qs, ty, col0, w, acc);
         if (a.include_center) {
 #pragma unroll
@@ -895,16 +879,6 @@ void stream_kernel(const IterArgs a) {
                                      acc[i][c]);
         }
     }, std::make_integer_sequence<int, NCH>{});
-    if constexpr (!FIRST) {
-        __builtin_amdgcn_s_waitcnt(vm_wait(0));
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < CM; ++c) {
-            const float2 t = *reinterpret_cast<const float2*>(Us + c * 1024 + ty * TW + col0);
-            u[0][c] = t.x;
-            u[1][c] = t.y;
-        }
-    }
     if (!pix_ok) return;
 
     // ---- compatibility, unary, softmax (Alg. 1), store Q_{t+1}
@@ -950,7 +924,7 @@ void stream_kernel(const IterArgs a) {
 
 template <int K, int CM, int CH>
 hipError_t launch_stream(const IterArgs& a, size_t lds, hipStream_t stream) {
-    auto fn = a.first ? stream_kernel<K, CM, CH, true> : stream_kernel<K, CM, CH, false>;
+    auto fn = stream_kernel<K, CM, CH>;
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(a.ntiles), dim3(512), lds, stream, a);
@@ -958,10 +932,12 @@ hipError_t launch_stream(const IterArgs& a, size_t lds, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------- ring update
-// The later iterations on half-height tiles (kStreamTW x kRingRows, 256
-// threads, two pixels each) so that two work-groups share a CU and one's
-// waits overlap the other's arithmetic.  As stream_kernel, but the class
-// chunks cycle through kRingSlots LDS slots (chunk k in slot k mod
+// The later iterations of narrow windows (k = 3, 5) with 19 or 21 classes:
+// half-height tiles (kStreamTW x kRingRows, 256 threads, two pixels each, all
+// taps of a pixel in its own thread).  At up to 24 taps a pixel the lane groups
+// of group.hip pay more for adding their partial messages than the wider LDS
+// reads give back (k = 5, 1 x 21 x 352 x 528: 14.8 us a round here, 16.4 there).
+// The class chunks cycle through kRingSlots LDS slots (chunk k in slot k mod
 // kRingSlots; one chunk per slot is issued at the start, then chunk
 // k + kRingSlots - 1 goes into the slot of chunk k - 1 once every wave is
 // past it) and each thread's unary comes straight into registers, issued
@@ -1241,20 +1217,16 @@ hipError_t launch_ring(const IterArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------- quad update (k = 7, Potts)
-// Rounds 2..T of the k = 7 update with Potts compatibility, on the ring's
-// tiles, staging and class-chunk ring, with a thread layout that cuts the
-// LDS bytes of the message (which bound ring_kernel's message loop): a pair
-// of lanes shares four horizontally adjacent pixels.  The even lane applies
-// window rows 0, 1, 2 and the left half of row 3, the odd lane rows 4, 5, 6
-// and the right half of row 3: 24 taps each, the centre excluded; each lane
-// picks its per-offset constants once per tap.  Per (class, window row) a
-// lane reads 10 staged floats (rows
-// padded to 16 bytes: two 16-byte reads and an 8-byte one) for 28 FMAs,
-// where the two-pixel layout reads 8 for 14.  After each chunk the pair adds
-// its two partial messages with one DPP lane swap per class and pixel: the
-// even lane keeps pixels 0 and 1, the odd lane pixels 2 and 3, and each then
-// runs ring_kernel's epilogue on its two.
+// ---------------------------------------- quad first round (k = 7, Potts)
+// A pair of lanes shares four horizontally adjacent pixels.  The even lane
+// applies window rows 0, 1, 2 and the left half of row 3, the odd lane rows
+// 4, 5, 6 and the right half of row 3: 24 taps each, the centre excluded;
+// each lane picks its per-offset constants once per tap.  Per (class, window
+// row) a lane reads 10 staged floats (rows padded to 16 bytes: two 16-byte
+// reads and an 8-byte one) for 28 FMAs, where the two-pixel layout of
+// stream_kernel reads 8 for 14.  After each chunk the pair adds its two
+// partial messages with one DPP lane swap per class and pixel: the even lane
+// keeps pixels 0 and 1, the odd lane pixels 2 and 3.
 template <int N>
 __device__ __forceinline__ void lds_row16(const float* p, float (&v)[N]) {
     static_assert(N % 2 == 0, "row length must be even");
@@ -1327,220 +1299,8 @@ __device__ __forceinline__ void quad_chunk(const float* Qs, unsigned rbase, unsi
     }
 }
 
-template <int CM, int CH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void quad_kernel(const IterArgs a) {
-    constexpr int K = 7, R = 3;
-    constexpr int TW = kStreamTW, ROWS = kRingRows, NWAVE = 4;
-    constexpr int LW = TW + 2 * R, LH = ROWS + 2 * R;
-    constexpr int LS = kQuadStride;
-    constexpr int PLANE = quad_plane();
-    constexpr int NI = PLANE / 64;               // 64-float loads per plane
-    constexpr int NJ = (NI + NWAVE - 1) / NWAVE; // per wave and plane
-    constexpr int NCH = (CM + CH - 1) / CH;
-    constexpr unsigned kOob = 0x80000000u;
-    static_assert(4 * 16 == TW && 2 * 16 * ROWS == 256, "16 pixel quads per row, a lane pair each");
-    extern __shared__ float4 smem4[];
-    float* const smem = reinterpret_cast<float*>(smem4);
-    float* const Qs = smem;                              // [kRingSlots][CH][PLANE]
-    float* const Cs = smem + kRingSlots * CH * PLANE;    // [3][PLANE]
-    float* const dummy = Cs + 3 * PLANE;                 // one 256-float row
-    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) float*)smem;
-    auto lds_addr = [&](const float* p) { return lds0 + (unsigned)((p - smem) * 4); };
-
-    const int H = a.H, W = a.W;
-    const int tile = xcd_tile(blockIdx.x, a.ntiles);
-    const int b = tile / a.tiles_per_img;
-    const int trem = tile - b * a.tiles_per_img;
-    const int tyi = trem / a.tiles_x;
-    const int y0 = tyi * ROWS;
-    const int x0 = (trem - tyi * a.tiles_x) * TW;
-    const size_t HW = (size_t)H * W;
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int half = tid & 1, ty = tid >> 5;
-    const int cq = 4 * ((tid >> 1) & 15);        // staged column of pixel 0's window
-    const int y = y0 + ty, xo = x0 + cq + 2 * half;   // the lane's two output pixels
-    const bool pix_ok = y < H && x0 + cq < W;    // W % 4 == 0: all four or none
-
-    // ---- colours, then the first chunks of Q_t (as ring_kernel)
-    unsigned voff[NJ];
-    int dst[NJ];
-#pragma unroll
-    for (int s = 0; s < NJ; ++s) {
-        const int j = wave + NWAVE * s;
-        const int f = j * 64 + lane;
-        const int r = f / LS, col = f - (f / LS) * LS;
-        const int gy = y0 - R + r, gx = x0 - R + col;
-        const bool in = j < NI && f < LH * LS && col < LW && gy >= 0 && gy < H && gx >= 0 && gx < W;
-        voff[s] = in ? (unsigned)((gy * W + gx) * 4) : kOob;
-        dst[s] = j < NI ? j * 64 : -1;
-    }
-    const rsrc_t rf = buffer_rsrc(a.feat + (size_t)b * 3 * HW, (unsigned)(3 * HW * 4));
-    const rsrc_t rq = buffer_rsrc(a.src + (size_t)b * CM * HW, (unsigned)(CM * HW * 4));
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch)
-#pragma unroll
-        for (int s = 0; s < NJ; ++s)
-            lds_dma(rf, voff[s], (int)(ch * HW * 4),
-                    lds_addr(dst[s] >= 0 ? Cs + ch * PLANE + dst[s] : dummy));
-    auto issue_chunk = [&](int k) {
-        const int c_lo = k * CH, c_hi = (k + 1) * CH < CM ? (k + 1) * CH : CM;
-        float* const slot = Qs + (k % kRingSlots) * CH * PLANE;
-        for (int c = c_lo; c < c_hi; ++c)
-#pragma unroll
-            for (int s = 0; s < NJ; ++s)
-                lds_dma(rq, voff[s], (int)(c * HW * 4),
-                        lds_addr(dst[s] >= 0 ? slot + (c - c_lo) * PLANE + dst[s] : dummy));
-    };
-    constexpr int A0 = kRingSlots, AHEAD = kRingSlots - 1;
-    static_for([&](auto kc) {
-        if constexpr (decltype(kc)::value < NCH) issue_chunk(decltype(kc)::value);
-    }, std::make_integer_sequence<int, A0>{});
-    auto chunk_loads = [](int k0, int n) {
-        int t = 0;
-        for (int j = k0; j < k0 + n; ++j) t += stream_chunk_loads(j, CM, CH, NJ);
-        return t;
-    };
-
-    // this lane's window rows: full rows R (half + 1) + j, j < R, at
-    // rbase + j LS, and the half row R at hbase
-    const unsigned rbase = (unsigned)((ty + (R + 1) * half) * LS + cq);
-    const unsigned hbase = (unsigned)((ty + R) * LS + cq + (R + 1) * half);
-
-    // ---- colours landed: the weights of the lane's 4 x 24 taps
-    __builtin_amdgcn_s_waitcnt(vm_wait(chunk_loads(0, A0)));
-    __syncthreads();
-    float w[4][4][K];
-    {
-        float own[3][4];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            float r[10];
-            lds_row16<10>(Cs + ch * PLANE + (ty + R) * LS + cq, r);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) own[ch][i] = r[R + i];
-        }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            float nc[3][10];
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) lds_row16<10>(Cs + ch * PLANE + rbase + j * LS, nc[ch]);
-#pragma unroll
-            for (int dx = 0; dx < K; ++dx) {
-                // |d|^2 of the tap for the even lane (row j) and the odd one (row R + 1 + j)
-                const int ne = (dx - R) * (dx - R) + (R - j) * (R - j);
-                const int no = (dx - R) * (dx - R) + (j + 1) * (j + 1);
-                float ae = a.taps.app_log2[ne], ao = a.taps.app_log2[no];
-                float se = a.taps.smooth[ne], so = a.taps.smooth[no];
-                asm volatile("" : "+s"(ae), "+s"(ao), "+s"(se), "+s"(so));
-                const float ca = half ? ao : ae;
-                const float cs = half ? so : se;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float d0 = own[0][i] - nc[0][i + dx];
-                    const float d1 = own[1][i] - nc[1][i + dx];
-                    const float d2 = own[2][i] - nc[2][i + dx];
-                    const float col2 = fmaf(d2, d2, fmaf(d1, d1, d0 * d0));
-                    w[j][i][dx] = __builtin_amdgcn_exp2f(fmaf(col2, a.neg_beta, ca)) + cs;
-                }
-            }
-        }
-        // the half row: taps dx = d (even lane) or R + 1 + d (odd lane)
-        float hc[3][6];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) lds_row16<6>(Cs + ch * PLANE + hbase, hc[ch]);
-#pragma unroll
-        for (int d = 0; d < R; ++d) {
-            const int nl = (R - d) * (R - d), nr = (d + 1) * (d + 1);
-            // both constants as scalars first, then the lane's choice
-            float al = a.taps.app_log2[nl], ar = a.taps.app_log2[nr];
-            float sl = a.taps.smooth[nl], sr = a.taps.smooth[nr];
-            asm volatile("" : "+s"(al), "+s"(ar), "+s"(sl), "+s"(sr));
-            const float ca = half ? ar : al;
-            const float cs = half ? sr : sl;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float d0 = own[0][i] - hc[0][i + d];
-                const float d1 = own[1][i] - hc[1][i + d];
-                const float d2 = own[2][i] - hc[2][i + d];
-                const float col2 = fmaf(d2, d2, fmaf(d1, d1, d0 * d0));
-                w[3][i][d] = __builtin_amdgcn_exp2f(fmaf(col2, a.neg_beta, ca)) + cs;
-            }
-        }
-    }
-
-    // keep the weights' arithmetic above the chunk loop, where the unary's
-    // registers are not yet live
-    __builtin_amdgcn_sched_barrier(0);
-    // the message of the lane's two pixels, completed chunk by chunk; the
-    // unary (Potts: Z = U + M) is loaded at the last chunk, where it first
-    // has registers to land in
-    float fin[2][CM];
-    float u[2][CM];
-    constexpr int UK = NCH - 1;
-    static_for([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        constexpr int c_lo = k * CH;
-        constexpr int c_hi = (k + 1) * CH < CM ? (k + 1) * CH : CM;
-        constexpr int last0 = k == 0 ? A0 - 1 : (A0 - 1 > k - 1 + AHEAD ? A0 - 1 : k - 1 + AHEAD);
-        constexpr int last = last0 < NCH - 1 ? last0 : NCH - 1;
-        constexpr int sk = k < A0 ? -1 : k - AHEAD;
-        __builtin_amdgcn_s_waitcnt(vm_wait(chunk_loads(k + 1, last - k) +
-                                           (sk <= UK && UK < k ? CM : 0)));
-        __syncthreads();
-        if constexpr (k + AHEAD < NCH && k + AHEAD > last) issue_chunk(k + AHEAD);
-        if constexpr (k == UK) {
-            // buffer loads: one lane offset and a scalar offset per class, so
-            // that no 64-bit address is held per class
-            const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(a.unary + (size_t)b * CM * HW), (short)0, (int)(CM * HW * 4), 0x00020000);
-            const int uoff = pix_ok ? (y * W + xo) * 4 : 0;
-#pragma unroll
-            for (int c = 0; c < CM; ++c) {
-                const auto t = __builtin_amdgcn_raw_buffer_load_b64(ru, uoff, (int)(c * HW * 4), 0);
-                u[0][c] = __int_as_float((int)t[0]);
-                u[1][c] = __int_as_float((int)t[1]);
-            }
-        }
-        float acc[4][c_hi - c_lo];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < c_hi - c_lo; ++c) acc[i][c] = 0.f;
-        const float* const qk = Qs + (k % kRingSlots) * CH * PLANE;
-        quad_chunk<PLANE, LS, c_lo, c_hi>(qk - c_lo * PLANE, rbase, hbase, w, acc);
-#pragma unroll
-        for (int c = 0; c < c_hi - c_lo; ++c)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float mine = half ? acc[2 + i][c] : acc[i][c];
-                const float send = half ? acc[i][c] : acc[2 + i][c];
-                fin[i][c_lo + c] = mine + pair_swap(send);
-                // materialised here: sunk to the epilogue, the add would keep
-                // both of its operands live through the remaining chunks
-                asm volatile("" : "+v"(fin[i][c_lo + c]));
-            }
-    }, std::make_integer_sequence<int, NCH>{});
-    __builtin_amdgcn_s_waitcnt(vm_wait(0));     // the unary
-    if (!pix_ok) return;
-
-    // ---- Potts: softmax(U + M), store Q_{t+1}
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int c = 0; c < CM; ++c) fin[i][c] += u[i][c];
-        softmax_regs<CM, true>(fin[i], CM);
-    }
-    float* __restrict__ qd = a.dst + (size_t)b * CM * HW + (size_t)y * W + xo;
-#pragma unroll
-    for (int c = 0; c < CM; ++c)
-        *reinterpret_cast<float2*>(qd + c * HW) = make_float2(fin[0][c], fin[1][c]);
-}
-
 // The first round of the k = 7 Potts update in the quad layout, on the
-// tiles of stream_kernel<..., FIRST> (64 x 16 pixels, 512 threads, all planes
+// tiles of stream_kernel (64 x 16 pixels, 512 threads, all planes
 // of U staged at once, softmax(U) applied to the staged halo tile in LDS).
 // Everything is on chip before the message, so its loop runs at the LDS
 // rate, which the quad layout lowers; each lane keeps the unary of its two
@@ -1738,15 +1498,6 @@ hipError_t launch_quad_first(const IterArgs& a, hipStream_t stream) {
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(a.ntiles), dim3(512), stream_lds_bytes(7, CM, false), stream, a);
-    return hipGetLastError();
-}
-
-template <int CM, int CH>
-hipError_t launch_quad(const IterArgs& a, hipStream_t stream) {
-    auto fn = quad_kernel<CM, CH>;
-    hipError_t e = allow_full_lds(fn);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(a.ntiles), dim3(256), ring_lds_bytes(7, CM, CH, false, 0), stream, a);
     return hipGetLastError();
 }
 
@@ -2233,13 +1984,14 @@ hipError_t CRF_CAT(launch_pmsg_k, CRF_K)(const IterArgs& a, int nchunks, size_t 
     return launch_pmsg_cm<CRF_K>(a, nchunks, lds, stream);
 }
 
-// Streamed updates are built for k = 3, 5, 7 and the class counts 19 and 21.
+// The streamed first iteration is built for k = 3, 5, 7 and the class counts
+// 19 and 21.
 hipError_t CRF_CAT(launch_stream_k, CRF_K)(const IterArgs& a, size_t lds, hipStream_t stream) {
     constexpr int K = CRF_K;
     if constexpr (K < 3 || K > 7) {
         return hipErrorNotSupported;
     } else {
-        if (a.mode != kModeUpdate || a.planes != a.C || !a.vec || (a.W & 3) ||
+        if (a.mode != kModeUpdate || !a.first || a.planes != a.C || !a.vec || (a.W & 3) ||
             reinterpret_cast<uintptr_t>(a.unary) % 16 != 0 ||
             (size_t)a.C * a.H * a.W * 4 >= (1ull << 31))
             return hipErrorNotSupported;
@@ -2251,11 +2003,10 @@ hipError_t CRF_CAT(launch_stream_k, CRF_K)(const IterArgs& a, size_t lds, hipStr
     }
 }
 
-// Ring updates: as the streamed ones, later iterations only (the source is
-// Q_t), on kStreamTW x kRingRows tiles.
+// Ring updates (k = 3, 5): the source is Q_t, on kStreamTW x kRingRows tiles.
 hipError_t CRF_CAT(launch_ring_k, CRF_K)(const IterArgs& a, hipStream_t stream) {
     constexpr int K = CRF_K;
-    if constexpr (K < 3 || K > 7) {
+    if constexpr (K < 3 || K > 5) {
         return hipErrorNotSupported;
     } else {
         if (a.mode != kModeUpdate || a.first || a.planes != a.C || !a.vec || (a.W & 3) ||
@@ -2271,19 +2022,6 @@ hipError_t CRF_CAT(launch_ring_k, CRF_K)(const IterArgs& a, hipStream_t stream) 
 }
 
 #if CRF_K == 7
-// Quad updates: the ring's rounds 2..T at k = 7 with Potts compatibility,
-// no centre tap and no learnable features.
-hipError_t launch_quad_k7(const IterArgs& a, hipStream_t stream) {
-    if (a.mode != kModeUpdate || a.first || a.planes != a.C || !a.vec || (a.W & 3) || a.mu ||
-        a.include_center || a.sfeat || (size_t)a.C * a.H * a.W * 4 >= (1ull << 31))
-        return hipErrorNotSupported;
-    switch (a.C) {
-        case 19: return launch_quad<19, 4>(a, stream);
-        case 21: return launch_quad<21, 3>(a, stream);
-        default: return hipErrorNotSupported;
-    }
-}
-
 // The first round in the quad layout on the streamed tiles (a.first, the
 // source U; the unary 16-byte aligned as for stream_kernel).
 hipError_t launch_quad_first_k7(const IterArgs& a, hipStream_t stream) {

@@ -52,6 +52,9 @@ def _units():
         if k >= 3:
             units.append((os.path.join(CSRC, "group.hip"), os.path.join(BUILD, f"group_k{k}.o"),
                           [f"-DCRF_GROUP_K={k}"]))
+        if 3 <= k <= 7:
+            units.append((os.path.join(CSRC, "adjoint.hip"), os.path.join(BUILD, f"adj_k{k}.o"),
+                          [f"-DCRF_ADJ_K={k}"]))
     for name in ("aux", "backward", "features", "api"):
         units.append((os.path.join(CSRC, f"{name}.hip"), os.path.join(BUILD, f"{name}.o"), []))
     return units

@@ -305,6 +305,15 @@ hipError_t launch_group(const GroupArgs& a, int k, hipStream_t s) {
     }
 }
 
+hipError_t launch_adj(const AdjArgs& a, int k, hipStream_t s) {
+    switch (k) {
+        case 3: return launch_adj_k3(a, s);
+        case 5: return launch_adj_k5(a, s);
+        case 7: return launch_adj_k7(a, s);
+        default: return hipErrorNotSupported;
+    }
+}
+
 hipError_t launch_resident(const IterArgs& a, int k, TileConfig t, size_t lds, int num_cus,
                            hipStream_t s, bool probe) {
     switch (k) {
@@ -1303,7 +1312,21 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     const float scale[5] = {1.f, (float)(s2 * p.w_app / (ta * ta * ta)),
                             (float)(p.w_app / (tb * tb * tb)), 1.f,
                             (float)(s2g * p.w_smooth / (tg * tg * tg))};
-    const int tw = bwd_tile_w(k), th = bwd_tile_h(k, C, D, dma, cgsize);
+    // Reverse rounds on lane groups (adjoint.hip): every class of a pixel in one
+    // work-group, the pointwise adjoints folded in.  A work-group's latency is the
+    // launch's where the tiles leave most of the card idle, and there the kernels
+    // that split the classes over work-groups are the faster ones: whole backward
+    // passes in us, classes split -> lane groups, k = 7: 20 tiles (80 x 48, T = 5)
+    // 163 -> 191, 108 tiles (2 x 108 x 117, T = 5) 223 -> 222, 228 tiles (227 x 215,
+    // T = 5, learned compatibility) 455 -> 350, 468 tiles (368 x 312, T = 3)
+    // 225 -> 163; k = 3, 44 tiles (2 x 88 x 48, T = 8) 199 -> 201.
+    const long long adj_tiles =
+        (long long)((W + kAdjTW - 1) / kAdjTW) * ((H + kAdjTH - 1) / kAdjTH) * B;
+    const bool adj = s == 1 && (k == 3 || k == 5 || k == 7) && group_ok(k, C, H, W) &&
+                     2 * adj_tiles >= ctx->num_cus;
+    const int tw = adj ? kAdjTW : bwd_tile_w(k);
+    const int th = adj ? kAdjTH : bwd_tile_h(k, C, D, dma, cgsize);
+    if (adj) groups = 1;
     const long long ntiles_ll = (long long)((Wg + tw - 1) / tw) * ((Hg + th - 1) / th) * B;
     if (ntiles_ll > 0x7fffffffLL) return fail(ctx, CONVCRF_E_UNSUPPORTED, "too many tiles");
     const int ntiles = (int)ntiles_ll;
@@ -1332,8 +1355,9 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     const size_t slice = (qbytes + 255) / 256 * 256;
     if ((st = ensure(ctx, ctx->b_q, slice * (iters + 1))) != CONVCRF_OK) return st;
     if (run) {
-        // dL/dQ^t ping-pong at full resolution (with blur it stays pooled)
-        if (s == 1 && (st = ensure(ctx, ctx->b_dq, slice * 2)) != CONVCRF_OK) return st;
+        // dL/dQ^t ping-pong at full resolution (with blur it stays pooled), or
+        // the second dL/dM of the lane-group rounds
+        if (s == 1 && (st = ensure(ctx, ctx->b_dq, slice * (adj ? 1 : 2))) != CONVCRF_OK) return st;
         if ((st = ensure(ctx, ctx->b_dm, slice)) != CONVCRF_OK) return st;
         if (grad_compat && !potts_dz)
             if ((st = ensure(ctx, ctx->b_dp, slice)) != CONVCRF_OK) return st;
@@ -1585,6 +1609,57 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     float* pdp = pdm ? pdm + pn : nullptr;
     float* pdq = pdm ? pdm + 2 * pn : nullptr;
     ba.dp = s > 1 ? (dp ? pdp : nullptr) : dp;
+    if (adj && run) {
+        AdjArgs aa{};
+        aa.image = image;
+        aa.dp = dp;
+        aa.dp_out = dp;
+        aa.sfeat = p.features;
+        aa.dfeat = df_grid;
+        aa.mu = mu_dev;
+        aa.du = grad_unary;
+        aa.gpart = ba.gpart;
+        aa.kpart = ba.kpart;
+        aa.dm_sum_scale = ba.dm_sum_scale;
+        aa.B = B;
+        aa.C = C;
+        aa.H = H;
+        aa.W = W;
+        aa.D = D;
+        aa.include_center = p.include_center;
+        aa.center_w = (float)((double)p.w_app + (double)p.w_smooth);
+        aa.neg_beta = ba.neg_beta;
+        aa.neg_gamma = ba.neg_gamma;
+        aa.inv_gamma2 = ba.inv_gamma2;
+        aa.w_app = p.w_app;
+        aa.w_smooth = p.w_smooth;
+        std::memcpy(aa.a_log2, ba.a_log2, sizeof(aa.a_log2));
+        std::memcpy(aa.smooth, ba.smooth, sizeof(aa.smooth));
+        float* cur = dm;
+        float* nxt = static_cast<float*>(ctx->b_dq.p);
+        // the last round's softmax, unary and compatibility; every other
+        // round's are folded into the adjoint message of the round after
+        st = launch(ctx, kBwdPoint, stream, "bwd_point", [&] {
+            return launch_bwd_point(qs(iters), grad_q, mu_dev, grad_unary, cur, dp, B, C,
+                                    (long long)H * W, 0, stream, W, 1);
+        });
+        if (st != CONVCRF_OK) return st;
+        for (int t = iters - 1; t >= 0; --t) {
+            aa.q = qs(t);
+            aa.dm = cur;
+            aa.dm_out = t > 0 ? nxt : nullptr;
+            aa.accumulate = t != iters - 1;
+            st = launch(ctx, kBwdMsg, stream, "bwd_message", [&] { return launch_adj(aa, k, stream); });
+            if (st != CONVCRF_OK) return st;
+            std::swap(cur, nxt);
+        }
+        if (grad_compat || grad_kernel)
+            return launch(ctx, kBwdReduce, stream, "bwd_reduce", [&] {
+                return launch_bwd_reduce(ba.gpart, ntiles, C, grad_compat, ba.kpart, ntiles, scale,
+                                         grad_kernel, stream);
+            });
+        return CONVCRF_OK;
+    }
     // dL/dQ^{t+1}: grad_q for the last round; with blur, the pooled adjoint of
     // the round after (dq_s = s), read in place through the pooling's transpose
     const float* dq = grad_q;

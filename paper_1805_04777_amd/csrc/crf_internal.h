@@ -493,6 +493,42 @@ hipError_t launch_bwd_msg_k11(const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_msg_k13(const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_msg_k15(const BwdArgs& a, hipStream_t stream);
 
+// ---- one reverse round on lane groups (adjoint.hip, k = 3, 5, 7): tiles of
+// kAdjTW x kAdjTH pixels, planes of kAdjPlane floats (one 16-byte load a lane),
+// kAdjCH classes of Q^t and of dL/dM^t a chunk, kAdjSlots chunks in LDS.
+constexpr int kAdjTW = 64, kAdjTH = 4, kAdjPlane = 1024, kAdjCH = 2, kAdjSlots = 3;
+inline size_t adj_lds_bytes(int CM, int FD, bool with_compat) {
+    const size_t stage = (size_t)(kAdjSlots * 2 * kAdjCH + 3 + FD) * kAdjPlane + kGroupTab +
+                         (with_compat ? (size_t)(CM * ((CM + 3) / 4 * 4) + 63) / 64 * 64 : 0);
+    return sizeof(float) * stage;              // the 2 CM x 257 floats of the product overlay it
+}
+static_assert(2 * 24 * 257 <= (kAdjSlots * 2 * kAdjCH + 3) * kAdjPlane, "the product's operands fit");
+struct AdjArgs {
+    const float* q;       // Q^t [B][C][H][W]
+    const float* dm;      // dL/dM^t
+    const float* image;   // [B][3][H][W]
+    const float* dp;      // -dL/dZ of the round (read with gpart when dm_sum_scale is 0)
+    const float* sfeat;   // learnable features [B][D][H][W], or null
+    const float* mu;      // device C x C compatibility, null = Potts
+    float* du;            // dL/dU, added to
+    float* dm_out;        // dL/dM^{t-1} (not dm), or null for t = 0
+    float* dp_out;        // its -dL/dZ (a given compatibility; may be dp), or null
+    float* dfeat;         // dL/dF [B][D][H][W] (with sfeat)
+    float* gpart;         // [ntiles][C * C] or null
+    float* kpart;         // [ntiles][5]
+    float dm_sum_scale;   // as in BwdArgs
+    int B, C, H, W, D;
+    int include_center;
+    int accumulate;       // add to kpart, gpart and dfeat instead of writing them
+    float center_w, neg_beta, neg_gamma, inv_gamma2, w_app, w_smooth;
+    float a_log2[kMaxN + 1];    // -n log2(e) / (2 theta_alpha^2)
+    float smooth[kMaxN + 1];    // exp(-n / (2 theta_gamma^2)), right behind a_log2
+    int tiles_x, tiles_per_img, ntiles;   // set by the launcher
+};
+hipError_t launch_adj_k3(AdjArgs a, hipStream_t stream);
+hipError_t launch_adj_k5(AdjArgs a, hipStream_t stream);
+hipError_t launch_adj_k7(AdjArgs a, hipStream_t stream);
+
 // Softmax, unary and compatibility adjoints of one round, per pixel:
 //   dZ = Q (dQ - <Q, dQ>);  du = dZ (+ du when accumulate);
 //   dm(l') = -sum_l mu[l][l'] dZ(l) (mu null = Potts) when dm is set;

@@ -147,35 +147,39 @@ def algorithmic_per_launch(kname: str, wl, D: int = 0):
         # product dP M^T (2C^2); reads Q^t, dM, dP and the image, writes dQ^t.
         # With features: the feature Gaussian (3D + 2), dk(x+d, x) (2C) and
         # dL/dF (2D + 4) per tap; the features read, dL/dF read and written
+        # With k = 3, 5, 7 the pointwise adjoints of the round before go with it:
+        # 7C more flops, dU read and written, dM written in place of dQ (not in
+        # the last launch).
+        pt = 7 * C if k in (3, 5, 7) else 0
+        pb = 8 * C - 4 * C / T if k in (3, 5, 7) else 4 * C
         if D:
-            return ((8 * C + 22 + 5 * D + 6) * taps + 2 * C * C) * px, (16 * C + 12 + 12 * D) * px
-        return (6 * C + 22) * taps * px + 2 * C * C * px, (16 * C + 12) * px
+            return (((8 * C + 22 + 5 * D + 6) * taps + 2 * C * C + pt) * px,
+                    (12 * C + pb + 12 + 12 * D) * px)
+        return ((6 * C + 22) * taps + 2 * C * C + pt) * px, (12 * C + pb + 12) * px
     if kname == "bwd_point":
+        if wl.blur == 1 and k in (3, 5, 7):
+            # one launch per call, the last round's: dot, dZ, dU and the Potts dM
+            # (7C flops); reads Q and grad_q, writes dU and dM
+            return 7 * C * px, 16 * C * px
         # T + 1 launches per call.  T undo a round: dot, dZ, dU and the Potts
         # dM (7C flops); read Q, dQ and, except on the first, dU; write dU
         # and dM (with Potts no -dZ plane is written).  The last one takes
         # only the initial softmax's adjoint (5C; read Q, dQ, dU, write dU).
         # dQ is grad_q on the first; with blur the later ones read it on the
-        # pooled grid (the pooling's transpose applied in place).
-        dq_later = 4 * C / (wl.blur * wl.blur)
-        rounds = 7 * C * T + 5 * C
-        rbytes = (12 * C * T + 4 * C + dq_later * (T - 1) + 4 * C * (T - 1)
+        # pooled grid (the pooling's transpose applied in place), and the T carry
+        # dM through the upsampling's transpose (8C flops) and write it pooled.
+        s2 = wl.blur * wl.blur
+        dq_later = 4 * C / s2
+        rounds = (7 + (8 if s2 > 1 else 0)) * C * T + 5 * C
+        rbytes = ((8 + 4 / s2) * C * T + 4 * C + dq_later * (T - 1) + 4 * C * (T - 1)
                   + 12 * C + dq_later)
         return rounds * px / (T + 1), rbytes * px / (T + 1)
     if kname == "bwd_reduce":
         return 0, 0
     if kname == "bwd_blur_transpose":
-        # one launch per round (with Potts -dL/dZ follows from dL/dM): the
-        # bilinear upsampling transposed for dL/dM, each full-resolution
-        # value reaching four cells (8 flop per pixel and class; the
-        # full-resolution planes read, the pooled ones written); with
-        # features one more at the end, the pooling's transpose of dL/dF
-        # (pooled read, full resolution written).  Averaged over the launches.
-        s2 = wl.blur * wl.blur
-        n = T + (1 if D else 0)
-        fl = 8 * C * px * T + D * px
-        by = 4 * (C * T + D) * (px + px / s2)
-        return fl / n, by / n
+        # one launch at the end with features: the pooling's transpose of dL/dF
+        # (pooled read, full resolution written)
+        return D * px, 4 * D * (px + px / (wl.blur * wl.blur))
     raise KeyError(kname)
 
 

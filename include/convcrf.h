@@ -246,14 +246,18 @@ convcrf_status convcrf_profile_enable(convcrf_ctx *ctx, int enable);
  * (the fused pooled message and update of one iteration, used for blur 4
  * instead of those two), and for
  * convcrf_meanfield_backward "bwd_point", "bwd_message", "bwd_reduce",
- * "bwd_blur_transpose" (with blur: the upsampling's transpose, one per reverse
- * round with Potts and two with a general compatibility, and with learnable
- * features one more for dL/dF through the pooling) besides the forward's;
+ * "bwd_blur_transpose" (dL/dF through the pooling, with blur and learnable
+ * features) besides the forward's; without blur "bwd_point" is launched once
+ * a call where "bwd_message" takes the pointwise adjoints of the round before
+ * as well (k = 3, 5, 7 on grids that fill half the card), else once a round
+ * and once for the softmax of the unary;
  * "feature_iter" with learnable
  * features, "fused_first") since profiling was enabled.  "fused_resident" is one
  * launch running all iterations of a call (CONVCRF_VARIANT_RESIDENT);
  * "fused_first" the first iteration of a fused call (it reads the unary and
- * applies the initial softmax on the fly) and "fused_iter" each later one.
+ * applies the initial softmax on the fly) and "fused_iter" each later one;
+ * where a separate pass is faster "softmax" takes its place and every iteration
+ * is a "fused_iter".
  * Synchronises on the recorded events.  An unknown or unused name gives
  * 0 ms and 0 launches. */
 convcrf_status convcrf_profile_read(convcrf_ctx *ctx, const char *name,

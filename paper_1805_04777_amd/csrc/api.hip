@@ -518,7 +518,8 @@ convcrf_status upload_mu(convcrf_ctx* ctx, const float* mu, int C, hipStream_t s
     const size_t n = (size_t)C * C;
     if (ctx->mu_last.size() == n && std::memcmp(ctx->mu_last.data(), mu, n * sizeof(float)) == 0)
         return CONVCRF_OK;
-    convcrf_status st = ensure(ctx, ctx->mu, n * sizeof(float));
+    // a row's worth more: kernels read rows of kMaxC floats
+    convcrf_status st = ensure(ctx, ctx->mu, (n + kMaxC) * sizeof(float));
     if (st != CONVCRF_OK) return st;
     hipError_t e;
     if (ctx->mu_pinned_cap < n) {
@@ -1358,8 +1359,9 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
         // dL/dQ^t ping-pong at full resolution (with blur it stays pooled), or
         // the second dL/dM of the lane-group rounds
         if (s == 1 && (st = ensure(ctx, ctx->b_dq, slice * (adj ? 1 : 2))) != CONVCRF_OK) return st;
-        if ((st = ensure(ctx, ctx->b_dm, slice)) != CONVCRF_OK) return st;
-        if (grad_compat && !potts_dz)
+        // (with blur dL/dM and -dL/dZ are stored pooled only)
+        if (s == 1 && (st = ensure(ctx, ctx->b_dm, slice)) != CONVCRF_OK) return st;
+        if (s == 1 && grad_compat && !potts_dz)
             if ((st = ensure(ctx, ctx->b_dp, slice)) != CONVCRF_OK) return st;
         if (grad_compat)
             if ((st = ensure(ctx, ctx->b_gpart, sizeof(float) * (size_t)ntiles * C * C)) !=
@@ -1599,7 +1601,8 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     }
     // Potts (C > 1): the compatibility derivative takes -dL/dZ from dL/dM,
     // so dL/dZ is neither written nor upsampled
-    float* dp = grad_compat && !potts_dz ? static_cast<float*>(ctx->b_dp.p) : nullptr;
+    const bool want_dp = grad_compat && !potts_dz;
+    float* dp = s == 1 && want_dp ? static_cast<float*>(ctx->b_dp.p) : nullptr;
     ba.dm_sum_scale = grad_compat && potts_dz ? (float)(1.0 / (1.0 - (double)C)) : 0.f;
     ba.gpart = grad_compat ? static_cast<float*>(ctx->b_gpart.p) : nullptr;
     float* dm = static_cast<float*>(ctx->b_dm.p);
@@ -1608,7 +1611,8 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     float* pdm = static_cast<float*>(ctx->b_pd.p);
     float* pdp = pdm ? pdm + pn : nullptr;
     float* pdq = pdm ? pdm + 2 * pn : nullptr;
-    ba.dp = s > 1 ? (dp ? pdp : nullptr) : dp;
+    if (!want_dp) pdp = nullptr;
+    ba.dp = s > 1 ? pdp : dp;
     if (adj && run) {
         AdjArgs aa{};
         aa.image = image;
@@ -1667,8 +1671,10 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
     for (int t = iters - 1; t >= 0; --t) {
         const int acc = t != iters - 1;
         st = launch(ctx, kBwdPoint, stream, "bwd_point", [&] {
-            return launch_bwd_point(qs(t + 1), dq, mu_dev, grad_unary, dm, dp, B, C,
-                                    (long long)H * W, acc, stream, W, dq_s);
+            return s > 1 ? launch_bwd_point_up(qs(t + 1), dq, mu_dev, grad_unary, pdm, pdp, B, C,
+                                               H, W, s, acc, dq_s, stream)
+                         : launch_bwd_point(qs(t + 1), dq, mu_dev, grad_unary, dm, dp, B, C,
+                                            (long long)H * W, acc, stream);
         });
         if (st != CONVCRF_OK) return st;
         float* dq_next = nullptr;
@@ -1688,19 +1694,8 @@ convcrf_status convcrf_meanfield_backward(convcrf_ctx* ctx, const float* unary,
             }
         } else {
             // M = upsample(pooled message of avgpool(Q^t)): the transpose of
-            // the upsampling (for dL/dM and, for dL/dmu, -dL/dZ), then the
-            // pooled adjoint message; the pooling's transpose is applied by
-            // the next bwd_point as it reads dL/dQ^t
-            st = launch(ctx, kBwdBlurT, stream, "bwd_blur_transpose", [&] {
-                return launch_upsample_t(dm, pdm, B, C, Hg, Wg, s, stream);
-            });
-            if (st != CONVCRF_OK) return st;
-            if (dp) {
-                st = launch(ctx, kBwdBlurT, stream, "bwd_blur_transpose", [&] {
-                    return launch_upsample_t(dp, pdp, B, C, Hg, Wg, s, stream);
-                });
-                if (st != CONVCRF_OK) return st;
-            }
+            // the upsampling went with the pointwise adjoints; the pooling's
+            // is applied by the next as it reads dL/dQ^t
             ba.q = pqs(t);
             ba.dm = pdm;
             ba.dq_out = pdq;

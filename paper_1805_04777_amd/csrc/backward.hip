@@ -13,9 +13,9 @@
 //                      recomputes the forward message M^t and sums
 //                      dP_p(l) M_p(l') over the tile's pixels.
 // bwd_reduce_kernel folds the per-tile partial sums; group_sum_kernel adds
-// the class groups' parts of dL/dF (learnable features).  upsample_t_kernel
-// and pool_t_kernel are the transposes of the blur variant's upsampling and
-// pooling.
+// the class groups' parts of dL/dF (learnable features).  With blur,
+// bwd_point_up_kernel is the pointwise adjoints and the transpose of the
+// upsampling in one, and pool_t_kernel the transpose of the pooling.
 //
 // Built once per window side k with -DCRF_BWD_K=k (the adjoint-message
 // kernels of that k) and once without (the pointwise and reduction kernels
@@ -434,6 +434,25 @@ hipError_t CONVCRF_BWD_CAT(launch_bwd_msg_k, CRF_BWD_K)(const BwdArgs& a, hipStr
 // S > 1: dL/dQ is given on the S x S pooled grid (the pooled adjoint of the
 // blur variant's message); pixel (y, x) takes its cell's value / S^2, the
 // transpose of the average pooling, read in place (W is the image width).
+// acc(l') = sum_l mu(l, l') (-dz(l)).  Row after row of mu, each one run of scalar
+// loads of CM floats (the last ends up to CM - C floats past the matrix, which
+// the buffer holds and no sum keeps): column after column took C scalar loads of
+// one float for C FMAs, and waited for them (2 x 21 x 240 x 320: 30 us a launch
+// of bwd_point_kernel, now 18).
+template <int CM>
+__device__ __forceinline__ void compat_t(const float* __restrict__ mu, const float* dz, int C,
+                                         float* acc) {
+#pragma unroll
+    for (int c = 0; c < CM; ++c) acc[c] = 0.f;
+#pragma unroll
+    for (int l = 0; l < CM; ++l)
+        if (l < C) {
+            const float* const row = mu + l * C;
+#pragma unroll
+            for (int c = 0; c < CM; ++c) acc[c] = fmaf(row[c], -dz[l], acc[c]);
+        }
+}
+
 template <int CM, int S>
 __global__ __launch_bounds__(256) void bwd_point_kernel(
     const float* __restrict__ q, const float* __restrict__ dq, const float* __restrict__ mu,
@@ -483,13 +502,11 @@ __global__ __launch_bounds__(256) void bwd_point_kernel(
     }
     if (!dm) return;
     if (mu) {
-        for (int lp = 0; lp < C; ++lp) {
-            float acc = 0.f;
+        float acc[CM];
+        compat_t<CM>(mu, dz, C, acc);
 #pragma unroll
-            for (int l = 0; l < CM; ++l)
-                if (l < C) acc = fmaf(mu[l * C + lp], -dz[l], acc);
-            dm[base + lp * hw] = acc;
-        }
+        for (int c = 0; c < CM; ++c)
+            if (c < C) dm[base + c * hw] = acc[c];
     } else {
         // Potts, mu[l][l'] = [l != l']: dm(l') = -(sum_l dZ(l) - dZ(l'))
 #pragma unroll
@@ -513,72 +530,139 @@ __device__ __forceinline__ float up_weight(int o, int cell, float inv_s, int n) 
     return (cell == a ? 1.f - f : 0.f) + (cell == i1 ? f : 0.f);
 }
 
+// The adjoints of the softmax, the unary addition and the compatibility transform
+// (bwd_point_kernel) followed by the transpose of the upsampling, on a tile of
+// kUpTW x kUpTH pixels: dL/dM never leaves the work-group at full resolution.
+//
 // Output o samples cell i0 = floor((o + 0.5) / s - 0.5) and i0 + 1, so the
 // full-resolution pixels that sample cell (Y, X) lie in rows [s Y - s/2,
-// s Y + 3s/2) and the same columns (the clamps at the edges only move
-// pixels inside that range onto the edge cells).  A work-group takes a
-// block of kUpTX x kUpTY cells of one plane: it stages the full-resolution
-// pixels under the block (zero outside the image) into LDS with coalesced
-// loads, then each thread sums the 2s x 2s window of its cell, row by row.
-constexpr int kUpTX = 64, kUpTY = 4;
+// s Y + 3s/2) and the same columns (the clamps at the edges only move pixels
+// inside that range onto the edge cells).  The tile is whole cells, so a thread
+// takes one pixel of the tile and its halo of s/2 (zero outside the image), writes
+// dL/dU if the pixel is the tile's, and leaves its dL/dM of all classes in LDS;
+// then each thread sums the 2s x 2s windows of its cells, row by row, and once more
+// with -dL/dZ for the compatibility derivative.  The halo is 1.2, 1.4 and 1.9 tiles
+// for s = 2, 4, 8: only Q^t is read for it.
+//
+// Bound by memory (Q^t, and dL/dU read and written).  32 x 16: two work-groups fit a
+// CU, so that one's loads pass under the other's sums, and 1 x 21 x 512 x 512 fills
+// the card with 512.  There, s = 4, Potts, per round: the pointwise kernel and the
+// transpose over a full-resolution dL/dM between them 15.5 + 12.3 us, this one 18.5
+// (20.2 with registers for one work-group a CU: 80 of them hold two at s = 4, the
+// other s have theirs anyway or no room in LDS).
+// DS: the resolution of dq (s pooled, 1 full).
+constexpr int kUpTW = 32, kUpTH = 16;
 template <int S>
-constexpr int up_cols() { return S * kUpTX + S; }
+constexpr int up_pix() { return (kUpTW + S) * (kUpTH + S); }
 template <int S>
-constexpr int up_rows() { return S * kUpTY + S; }
-template <int S>
-__global__ __launch_bounds__(256) void upsample_t_kernel(const float* __restrict__ in,
-                                                         float* __restrict__ out, int Hp,
-                                                         int Wp, int nbx, int nby) {
-    constexpr int h = S / 2, NX = 2 * S, COLS = up_cols<S>(), ROWS = up_rows<S>();
-    extern __shared__ float st[];                 // [ROWS][COLS]
-    const int H = Hp * S, W = Wp * S;
-    const long long blk = blockIdx.x;
-    const long long plane = blk / ((long long)nbx * nby);
-    const int rem = (int)(blk - plane * nbx * nby);
-    const int by = rem / nbx, bx = rem - by * nbx;
-    const int X0 = bx * kUpTX, Y0 = by * kUpTY;
-    const int gy0 = S * Y0 - h, gx0 = S * X0 - h;
-    const float* src = in + plane * H * W;
-    // every load of the thread issued before the first LDS store
-    constexpr int NE = (ROWS * COLS + 255) / 256;
-    float v[NE];
+constexpr int up_threads() { return (up_pix<S>() + 63) / 64 * 64; }
+template <int CM, int S, int DS>
+__global__ __launch_bounds__(up_threads<S>(), S == 4 ? 6 : 1) void bwd_point_up_kernel(
+    const float* __restrict__ q, const float* __restrict__ dq, const float* __restrict__ mu,
+    float* __restrict__ du, float* __restrict__ pdm, float* __restrict__ pdp, int C, int H, int W,
+    int accumulate, int tiles_x, int tiles_per_img, int ntiles) {
+    constexpr int h = S / 2, PW = kUpTW + S, NP = up_pix<S>(), NT = up_threads<S>();
+    extern __shared__ float4 st4[];
+    float* const st = reinterpret_cast<float*>(st4);   // [C][kUpTH + S][PW]
+    const int tile = xcd_tile(blockIdx.x, ntiles);
+    const int b = tile / tiles_per_img, trem = tile - b * tiles_per_img;
+    const int tyi = trem / tiles_x;
+    const int y0 = tyi * kUpTH, x0 = (trem - tyi * tiles_x) * kUpTW;
+    const int Hp = H / S, Wp = W / S;
+    const long long hw = (long long)H * W, phw = (long long)Hp * Wp;
+    const int ly = (int)threadIdx.x / PW, lx = (int)threadIdx.x - ly * PW;
+    const int y = y0 - h + ly, x = x0 - h + lx;
+    const bool in = threadIdx.x < NP && y >= 0 && y < H && x >= 0 && x < W;
+    const bool own = in && ly >= h && ly < h + kUpTH && lx >= h && lx < h + kUpTW;
+    const long long base = b * C * hw + (in ? (long long)y * W + x : 0);
+    const long long dbase =
+        DS == 1 ? base : b * C * phw + (in ? (long long)(y / S) * Wp + x / S : 0);
+    const long long dstride = DS == 1 ? hw : phw;
+    constexpr float inv = 1.f / (float)(DS * DS);
+    // every load issued before the first is used (classes past C re-read the
+    // last class and are dropped)
+    float qv[CM], dz[CM], uo[CM];
 #pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int e = threadIdx.x + 256 * k;
-        const int ly = e / COLS, lx = e - ly * COLS;
-        const int gy = gy0 + ly, gx = gx0 + lx;
-        const bool ok = e < ROWS * COLS && gy >= 0 && gy < H && gx >= 0 && gx < W;
-        v[k] = ok ? src[(long long)gy * W + gx] : 0.f;
+    for (int c = 0; c < CM; ++c) {
+        const int cc = c < C ? c : C - 1;
+        qv[c] = q[base + cc * hw];
+        dz[c] = DS > 1 ? dq[dbase + cc * dstride] * inv : dq[dbase + cc * dstride];
     }
+    if (accumulate && own) {
 #pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int e = threadIdx.x + 256 * k;
-        if (e < ROWS * COLS) st[e] = v[k];
+        for (int c = 0; c < CM; ++c) uo[c] = du[base + (c < C ? c : C - 1) * hw];
+    } else {
+#pragma unroll
+        for (int c = 0; c < CM; ++c) uo[c] = 0.f;
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int c = 0; c < CM; ++c)
+        if (c < C) dot = fmaf(qv[c], dz[c], dot);
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < CM; ++c) {
+        if (c < C) {
+            dz[c] = qv[c] * (dz[c] - dot);
+            sum += dz[c];
+            if (own) du[base + c * hw] = accumulate ? uo[c] + dz[c] : dz[c];
+        }
+    }
+    if (threadIdx.x < NP) {
+        float* const o = st + threadIdx.x;
+        if (mu) {
+            float acc[CM];
+            compat_t<CM>(mu, dz, C, acc);
+#pragma unroll
+            for (int c = 0; c < CM; ++c)
+                if (c < C) o[c * NP] = in ? acc[c] : 0.f;
+        } else {
+            // Potts, mu[l][l'] = [l != l']: dm(l') = -(sum_l dZ(l) - dZ(l'))
+#pragma unroll
+            for (int c = 0; c < CM; ++c)
+                if (c < C) o[c * NP] = in ? dz[c] - sum : 0.f;
+        }
     }
     __syncthreads();
-    const int tx = threadIdx.x % kUpTX, ty = threadIdx.x / kUpTX;
-    const int X = X0 + tx, Y = Y0 + ty;
-    if (X >= Wp || Y >= Hp) return;
-    const float inv_s = 1.f / (float)S;
-    float wx[NX];
+    auto gather = [&](float* __restrict__ out) {
+        constexpr int CX = kUpTW / S, CELLS = CX * (kUpTH / S), NX = 2 * S;
+        const float inv_s = 1.f / (float)S;
+        for (int i = threadIdx.x; i < C * CELLS; i += NT) {
+            const int c = i / CELLS, cell = i - c * CELLS;
+            const int ty = cell / CX, tx = cell - ty * CX;
+            const int X = x0 / S + tx, Y = y0 / S + ty;
+            if (X >= Wp || Y >= Hp) continue;
+            float wx[NX];
 #pragma unroll
-    for (int j = 0; j < NX; ++j) {
-        const int x = S * X - h + j;
-        wx[j] = x >= 0 && x < W ? up_weight(x, X, inv_s, Wp) : 0.f;
+            for (int j = 0; j < NX; ++j) {
+                const int xx = S * X - h + j;
+                wx[j] = xx >= 0 && xx < W ? up_weight(xx, X, inv_s, Wp) : 0.f;
+            }
+            float acc = 0.f;
+#pragma unroll
+            for (int jy = 0; jy < NX; ++jy) {
+                const int yy = S * Y - h + jy;
+                if (yy < 0 || yy >= H) continue;
+                const float wy = up_weight(yy, Y, inv_s, Hp);
+                const float* row = st + c * NP + (S * ty + jy) * PW + S * tx;
+                float t = 0.f;
+#pragma unroll
+                for (int j = 0; j < NX; ++j) t = fmaf(wx[j], row[j], t);
+                acc = fmaf(wy, t, acc);
+            }
+            out[(((long long)b * C + c) * Hp + Y) * Wp + X] = acc;
+        }
+    };
+    gather(pdm);
+    if (!pdp) return;
+    __syncthreads();
+    if (threadIdx.x < NP) {
+#pragma unroll
+        for (int c = 0; c < CM; ++c)
+            if (c < C) st[c * NP + threadIdx.x] = in ? -dz[c] : 0.f;
     }
-    float acc = 0.f;
-#pragma unroll
-    for (int jy = 0; jy < NX; ++jy) {
-        const int y = S * Y - h + jy;
-        if (y < 0 || y >= H) continue;
-        const float wy = up_weight(y, Y, inv_s, Hp);
-        const float* row = st + (S * ty + jy) * COLS + S * tx;
-        float t = 0.f;
-#pragma unroll
-        for (int j = 0; j < NX; ++j) t = fmaf(wx[j], row[j], t);
-        acc = fmaf(wy, t, acc);
-    }
-    out[(plane * Hp + Y) * Wp + X] = acc;
+    __syncthreads();
+    gather(pdp);
 }
 
 // blockIdx.y strides over the B * C * H full-resolution rows, kPoolTRows at
@@ -738,32 +822,46 @@ hipError_t launch_bwd_point(const float* q, const float* dq, const float* mu, fl
     return hipGetLastError();
 }
 
-template <int S>
-hipError_t launch_up_t(const float* in, float* out, int B, int C, int Hp, int Wp,
-                       hipStream_t stream) {
-    const int nbx = (Wp + kUpTX - 1) / kUpTX, nby = (Hp + kUpTY - 1) / kUpTY;
-    const long long blocks = (long long)B * C * nbx * nby;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t lds = sizeof(float) * up_rows<S>() * up_cols<S>();
-    auto fn = upsample_t_kernel<S>;
+template <int CM, int S, int DS>
+hipError_t launch_point_up_cs(const float* q, const float* dq, const float* mu, float* du,
+                              float* pdm, float* pdp, int B, int C, int H, int W, int accumulate,
+                              hipStream_t stream) {
+    const long long tx = (W + kUpTW - 1) / kUpTW, ty = (H + kUpTH - 1) / kUpTH;
+    if (tx * ty * B > 0x7fffffffLL) return hipErrorInvalidValue;
+    const size_t lds = sizeof(float) * up_pix<S>() * C;
+    auto fn = bwd_point_up_kernel<CM, S, DS>;
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(256), lds, stream, in, out, Hp, Wp, nbx,
-                       nby);
+    const int nt = (int)(tx * ty * B);
+    hipLaunchKernelGGL(fn, dim3(nt), dim3(up_threads<S>()), lds, stream, q, dq, mu, du, pdm, pdp,
+                       C, H, W, accumulate, (int)tx, (int)(tx * ty), nt);
     return hipGetLastError();
 }
 
-hipError_t launch_upsample_t(const float* in, float* out, int B, int C, int Hp, int Wp, int s,
-                             hipStream_t stream) {
-    if ((long long)B * C * Hp * Wp == 0) return hipSuccess;
+template <int S>
+hipError_t launch_point_up_s(const float* q, const float* dq, const float* mu, float* du,
+                             float* pdm, float* pdp, int B, int C, int H, int W, int accumulate,
+                             int dq_s, hipStream_t stream) {
+    auto fn = C <= 8 ? (dq_s == 1 ? launch_point_up_cs<8, S, 1> : launch_point_up_cs<8, S, S>)
+                     : (dq_s == 1 ? launch_point_up_cs<kMaxC, S, 1>
+                                  : launch_point_up_cs<kMaxC, S, S>);
+    return fn(q, dq, mu, du, pdm, pdp, B, C, H, W, accumulate, stream);
+}
+
+hipError_t launch_bwd_point_up(const float* q, const float* dq, const float* mu, float* du,
+                               float* pdm, float* pdp, int B, int C, int H, int W, int s,
+                               int accumulate, int dq_s, hipStream_t stream) {
+    if ((long long)B * C * H * W == 0) return hipSuccess;
+    if (C < 1 || C > kMaxC || (dq_s != 1 && dq_s != s) || H % s != 0 || W % s != 0)
+        return hipErrorInvalidValue;
     switch (s) {
-        case 2: return launch_up_t<2>(in, out, B, C, Hp, Wp, stream);
-        case 4: return launch_up_t<4>(in, out, B, C, Hp, Wp, stream);
-        case 8: return launch_up_t<8>(in, out, B, C, Hp, Wp, stream);
+        case 2: return launch_point_up_s<2>(q, dq, mu, du, pdm, pdp, B, C, H, W, accumulate, dq_s, stream);
+        case 4: return launch_point_up_s<4>(q, dq, mu, du, pdm, pdp, B, C, H, W, accumulate, dq_s, stream);
+        case 8: return launch_point_up_s<8>(q, dq, mu, du, pdm, pdp, B, C, H, W, accumulate, dq_s, stream);
         default: return hipErrorInvalidValue;
     }
 }

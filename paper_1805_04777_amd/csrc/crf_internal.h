@@ -540,12 +540,14 @@ hipError_t launch_bwd_point(const float* q, const float* dq, const float* mu, fl
                             float* dm, float* dp, int B, int C, long long HW,
                             int accumulate, hipStream_t stream, int W = 0, int s = 1);
 
-// Blur transposes (the pooled message of Sec. 4.2), [B][C] planes:
-// out [Hp][Wp] = the transpose of the bilinear x s upsampling (half-pixel
-// centres, edge clamp) of in [Hp s][Wp s]: each cell gathers the values
-// interpolated from it, with the same weights;
-hipError_t launch_upsample_t(const float* in, float* out, int B, int C, int Hp, int Wp, int s,
-                             hipStream_t stream);
+// Blur (the pooled message of Sec. 4.2): launch_bwd_point on an image of H x W
+// pixels, dq at full resolution (dq_s = 1) or on the s x s pooled grid (dq_s = s),
+// with dL/dM (and -dL/dZ, if pdp is set) carried through the transpose of the
+// bilinear x s upsampling (half-pixel centres, edge clamp) to the pooled grid: each
+// cell gathers the values interpolated from it, with the same weights.
+hipError_t launch_bwd_point_up(const float* q, const float* dq, const float* mu, float* du,
+                               float* pdm, float* pdp, int B, int C, int H, int W, int s,
+                               int accumulate, int dq_s, hipStream_t stream);
 // out [Hp s][Wp s] = the transpose of the s x s average pooling of in
 // [Hp][Wp]: each pixel receives its cell's value / s^2.
 hipError_t launch_pool_t(const float* in, float* out, int B, int C, int Hp, int Wp, int s,

@@ -87,3 +87,39 @@ def test_lane_group_adjoint(crf, oracle_mod, B, C, k, H, W, T, compat, D, center
     err, scale = np.abs(dk - rk), np.abs(rk).max()
     assert np.all(err <= np.where(np.abs(rk) >= 1e-2 * scale, TOL_PARAM * np.abs(rk),
                                   TOL_REL * scale)), (dk, rk)
+
+
+# (B, C, k, H, W, T, blur, compat): one cell, cells past a 32 x 16 tile, a tile exactly,
+# class counts at the two register bounds
+BLUR_CASES = [
+    (1, 1, 3, 2, 2, 2, 2, False), (2, 9, 3, 18, 34, 2, 2, True), (1, 24, 5, 14, 62, 1, 2, False),
+    (3, 8, 5, 4, 4, 3, 4, True), (1, 24, 3, 16, 32, 2, 4, True), (2, 21, 7, 20, 68, 2, 4, False),
+    (1, 2, 3, 8, 8, 3, 8, True), (1, 24, 3, 24, 40, 2, 8, False), (2, 22, 5, 16, 72, 2, 8, True),
+]
+
+
+@pytest.mark.parametrize("B,C,k,H,W,T,s,compat", BLUR_CASES)
+def test_blur_point_and_transpose(crf, oracle_mod, B, C, k, H, W, T, s, compat):
+    """The pointwise adjoints with the transpose of the upsampling in the same launch."""
+    import torch
+    from paper_1805_04777_amd import convcrf as cc
+    rng = np.random.default_rng(9500 + 100 * s + C + H + W)
+    U = rng.normal(0.0, 1.5, (B, C, H, W)).astype(np.float32)
+    I = np.clip(np.rint(rng.uniform(0, 200, (B, 3, 1, 1)) + rng.normal(0, 15, (B, 3, H, W))),
+                0, 255).astype(np.float32)
+    G = rng.normal(0.0, 1.0, (B, C, H, W)).astype(np.float32)
+    mu = synth.random_compat(C, seed=k) if compat else None
+    kw = dict(filter_size=k, blur=s, w_app=30.0 / k ** 2, w_smooth=9.0 / k ** 2)
+    t = lambda a: torch.from_numpy(a).cuda()
+    got = crf.meanfield_backward(t(U), t(I), cc.Params(compat=mu, **kw), T, t(G),
+                                 grad_compat=True, grad_kernel=True)
+    torch.cuda.synchronize()
+    got = [x.cpu().numpy().astype(np.float64) for x in got]
+    ref = oracle_mod.meanfield_backward(U, I, OracleParams(**kw), T, G, compat=mu)
+    for name, a, b in zip(("dU", "dmu"), got, ref):
+        assert np.abs(a - b).max() <= TOL_REL * np.abs(b).max(), name
+    scale = np.abs(ref[2]).max()
+    big = np.abs(ref[2]) >= 1e-2 * scale
+    err = np.abs(got[2] - ref[2])
+    assert np.all(err[big] <= TOL_PARAM * np.abs(ref[2])[big]), (got[2], ref[2])
+    assert np.all(err <= TOL_REL * scale + 1e-30) or np.all(err[~big] <= TOL_REL * scale)

@@ -217,8 +217,8 @@ convcrf_status convcrf_meanfield_noalloc(convcrf_ctx *ctx, const float *unary,
  * unary, image, grad_q: DEVICE pointers, as for convcrf_meanfield; grad_q
  * [B][C][H][W].  grad_unary must not overlap unary, image or grad_q.
  * The context's workspace grows by (iters + 1) + 1 buffers of [B][C][H][W]
- * floats (Q^0..Q^T, dL/dM), two more for dL/dQ without blur (with blur it
- * stays on the pooled grid), one more (-dL/dZ) with grad_compat and a general
+ * floats (Q^0..Q^T, and without blur dL/dM), without blur up to two more for
+ * dL/dQ or a second dL/dM and one (-dL/dZ) with grad_compat and a general
  * compatibility, with blur the pooled Q^t of every round and three pooled
  * adjoint tensors, and per-tile partial sums.
  * Returns CONVCRF_E_UNSUPPORTED when the window and classes exceed the LDS of
